@@ -5,16 +5,21 @@ kernels of ``libbifattn.so``. The functions carry the C ABI's names
 (include/bifattn.h); torch tensors are checked against the plan's shape,
 dtype, device and contiguity before their device pointers are handed over,
 so a mismatched tensor is refused on the host instead of being read out of
-bounds on the GPU. There is no fallback: without the built library every
-entry point raises.
+bounds on the GPU. The per-step calls (decode, append) first go through the
+same checks in native code (``_bifattn_bind.so``), which leaves every call it
+does not take to the checks here. There is no fallback: without the built
+libraries every entry point raises.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libbifattn.so")
+BIND_PATH = os.path.join(_HERE, "_bifattn_bind.so")
 
 OK, EINVAL, EUNSUPPORTED, EALIGN, ENOMEM, EHIP, ELENS, ESCALE, ESCRATCH = 0, -1, -2, -3, -4, -5, -6, -7, -8
 #: Size of the fixed device scratch of bifattn_decode_noalloc (BIFATTN_NOALLOC_SCRATCH_BYTES).
@@ -100,6 +105,36 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+_bind = None
+
+
+def _bind_module():
+    """The native argument checks (_bifattn_bind.so, built in-tree)."""
+    global _bind
+    if _bind is None:
+        if not os.path.exists(BIND_PATH):
+            raise RuntimeError(f"{BIND_PATH} is missing: build it with "
+                               "`python -m paper_2403_08845_amd.build`")
+        import torch  # noqa: F401  (its libraries are the module's)
+        loader = importlib.machinery.ExtensionFileLoader("_bifattn_bind", BIND_PATH)
+        mod = importlib.util.module_from_spec(importlib.util.spec_from_loader("_bifattn_bind", loader))
+        loader.exec_module(mod)
+        _bind = mod
+    return _bind
+
+
+def _caller(dims, handle, device_index):
+    """The native caller of a plan's per-step entry points."""
+    import torch
+    L = lib()
+    addr = [ctypes.cast(f, ctypes.c_void_p).value
+            for f in (L.bifattn_decode_scaled, L.bifattn_append_kv)]
+    D = dims
+    return _bind_module().Caller(*addr, handle.value, torch._C._cuda_getCurrentRawStream,
+                                 device_index, D.b, D.h, D.g, D.d, D.m_c, D.m_d_max, max(1, D.n),
+                                 D.kv_type)
+
+
 def status_string(status: int) -> str:
     return lib().bifattn_status_string(int(status)).decode()
 
@@ -133,8 +168,10 @@ class Plan:
         #: The device the plan's workspace lives on (current at creation):
         #: every tensor and the stream of a call must belong to it.
         self.device = torch.device("cuda", torch.cuda.current_device())
+        self._caller = _caller(self.dims, handle, self.device.index)
 
     def close(self):
+        self._caller = None
         if getattr(self, "handle", None) is not None and self.handle.value:
             _check(lib().bifattn_plan_destroy(self.handle), "bifattn_plan_destroy")
             self.handle = None
@@ -259,6 +296,14 @@ def bifattn_decode_scaled(plan: Plan, q, Kc, Vc, Kd, Vd, decode_lens, k_scale, v
                           stream=None):
     """bifattn_decode with per-group key / value scales (fp32 [g] tensors on
     the GPU, or None for 1)."""
+    caller = getattr(plan, "_caller", None)
+    if caller is not None:
+        st = caller.decode(q, Kc, Vc, Kd, Vd, decode_lens, k_scale, v_scale, out,
+                           None if stream is None else _stream_ptr(stream).value or 0)
+        if st is not None:
+            if st != OK:
+                raise BifattnError(st, "bifattn_decode_scaled")
+            return
     import torch
     D = plan.dims
     dev = plan.device
@@ -352,6 +397,14 @@ def bifattn_append_kv(plan: Plan, k_new, v_new, Kd, Vd, decode_lens, stream=None
     k_new, v_new [b,g,n,d] go to rows decode_lens[i] .. + n - 1 of
     Kd, Vd [b,g,m_d_max,d] (the plan's cache type); decode_lens int32 [b]
     advances by n."""
+    caller = getattr(plan, "_caller", None)
+    if caller is not None:
+        st = caller.append(k_new, v_new, Kd, Vd, decode_lens,
+                           None if stream is None else _stream_ptr(stream).value or 0)
+        if st is not None:
+            if st != OK:
+                raise BifattnError(st, "bifattn_append_kv")
+            return
     import torch
     D = plan.dims
     dev = plan.device

@@ -1,16 +1,19 @@
-"""Build libbifattn.so for gfx950 in-tree with hipcc.
+"""Build libbifattn.so for gfx950 in-tree with hipcc, and the Python
+binding's native part with the host compiler.
 
     python -m paper_2403_08845_amd.build
 
 Compiles the HIP kernels and the host-side C ABI into
 ``paper_2403_08845_amd/libbifattn.so``. Packed fp32 VALU instructions are
-disabled for all device code.
+disabled for all device code. ``_bifattn_bind.so`` beside it (host code only,
+against torch's headers) checks the arguments of the per-step calls.
 """
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -18,6 +21,8 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libbifattn.so")
 SOURCES = [os.path.join(CSRC, "bifattn_kernels.hip"), os.path.join(CSRC, "bifattn_host.cpp")]
+BIND_SRC = os.path.join(CSRC, "bifattn_bind.cpp")
+BIND = os.path.join(HERE, "_bifattn_bind.so")
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
@@ -37,19 +42,38 @@ def hipcc() -> str:
     return "hipcc"
 
 
-def build(verbose: bool = False) -> str:
-    tmp = LIB + ".tmp"
-    cmd = [hipcc(), *HIPCC_FLAGS, *SOURCES, "-o", tmp]
+def _run(cmd, verbose: bool) -> None:
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"
     err = "\n".join(l for l in (res.stderr or "").splitlines() if noise not in l)
     if res.returncode != 0:
-        raise RuntimeError(f"hipcc failed ({res.returncode}):\n{err}")
+        raise RuntimeError(f"{cmd[0]} failed ({res.returncode}):\n{err}")
     if verbose and err.strip():
         print(err, file=sys.stderr)
+
+
+def build_bind(verbose: bool = False) -> str:
+    import torch
+    from torch.utils.cpp_extension import include_paths, library_paths
+    tmp = BIND + ".tmp"
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc())))
+    dirs = [INCLUDE, os.path.join(rocm, "include"), sysconfig.get_paths()["include"], *include_paths()]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D__HIP_PLATFORM_AMD__", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *[f"-I{d}" for d in dirs], BIND_SRC, "-o", tmp,
+           *[f"-L{d}" for d in library_paths()], "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    _run(cmd, verbose)
+    os.replace(tmp, BIND)
+    return BIND
+
+
+def build(verbose: bool = False) -> str:
+    tmp = LIB + ".tmp"
+    _run([hipcc(), *HIPCC_FLAGS, *SOURCES, "-o", tmp], verbose)
     os.replace(tmp, LIB)
+    build_bind(verbose)
     return LIB
 
 
