@@ -115,11 +115,11 @@ bool on_plan_device(const bifattn_plan_s* P, hipStream_t stream) {
 // Keys one decode work-group reads: the whole decode cache up to 1024 keys
 // (each work-group writes partials for p rows per wave, so short chunks
 // multiply that traffic, and ragged lengths leave short chunks nearly empty),
-// halved (down to 128) only while fewer than half as many work-groups as
-// CUs would exist.
-int dec_chunk_keys(int64_t units, int64_t rows) {
+// halved (never below `least`) only while fewer than half as many work-groups
+// as CUs would exist.
+int dec_chunk_keys(int64_t units, int64_t rows, int least) {
   int keys = (int)std::min<int64_t>(1024, std::max<int64_t>(128, round_up(rows, 128)));
-  while (keys > 128 && units * ceil_div(rows, keys) < kCUs / 2) keys /= 2;
+  while (keys / 2 >= least && units * ceil_div(rows, keys) < kCUs / 2) keys /= 2;
   return keys;
 }
 // Rounding of the many-row context chunk: the wide kernel runs 128-key
@@ -139,7 +139,9 @@ int seq_keys(int64_t units, int64_t rows, int start) {
 
 // allow_fork: the many-row path may run the decode launch on the plan's own
 // stream (off for the allocation-free entry point, which owns no stream).
-bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true) {
+// coarse: the longest chunks (the allocation-free entry point's limit counts
+// these, and it takes them where shorter ones' partials pass the scratch).
+bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coarse = false) {
   const bifattn_dims_t& d = P->dims;
   P->ntok = d.n > 0 ? d.n : 1;
   // The n tokens of a head are consecutive rows of q and out, so a unit's
@@ -151,14 +153,27 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true) {
   const int64_t units = (int64_t)d.b * d.g;
   if (M <= 64) {
     // Few rows per group: S_c work-groups per group, interleaved over the
-    // group's tiles; about four of them, each with 1024..2048 keys (2-4
-    // decode work-groups' worth): fewer, longer context work-groups leave
-    // fewer partials to merge, too few stop covering the decode part's time.
+    // group's tiles. Where the step fills the GPU, about four of them, each
+    // with 1024..2048 keys (2-4 decode work-groups' worth): fewer, longer
+    // context work-groups leave fewer partials to merge, too few stop
+    // covering the decode part's time. A step that leaves slots idle (two
+    // work-groups per CU) is as long as its longest work-group, so it takes
+    // chunks of about twice the keys that an even split over the slots would
+    // give each, down to 256 (shorter ones cost the combine more than they
+    // save). Measured, long chunks against these (us per step, bf16, d = 128):
+    // b 5, h 32, g 8, m_c 3001 19.7 -> 13.8; m_c 12000 29.6 -> 19.8; b 20,
+    // h 8, g 4, m_c 25000 44.6 -> 30.3; b 16, h = g = 32, m_c 8192, m_d 256
+    // 38.0 -> 37.1 (1536 keys; 1024: 40.1).
     P->ctx_mode = M <= 16 ? kCtxSmall1 : (M <= 32 ? kCtxSmall2 : kCtxSmall4);
-    const int64_t quarter = round_up(ceil_div(d.m_c, 4), kWaves * kTileKeys);
-    const int def_keys = (int)std::min<int64_t>(2048, std::max<int64_t>(1024, quarter));
-    const int keys = (int)round_up(env_int("BIFATTN_CTX_KEYS", def_keys), kWaves * kTileKeys);
-    P->ctx_keys = keys;
+    constexpr int step = kWaves * kTileKeys;
+    const int64_t quarter = round_up(ceil_div(d.m_c, 4), step);
+    int64_t keys = std::min<int64_t>(2048, std::max<int64_t>(1024, quarter));
+    if (!coarse) {
+      const int64_t all = (int64_t)d.g * d.m_c + units * d.m_d_max;  // keys of every unit
+      const int64_t even = std::max<int64_t>(256, ceil_div(2 * all, 2 * kCUs));
+      if (even < keys) keys = round_up(ceil_div(d.m_c, ceil_div(d.m_c, even)), step);
+    }
+    P->ctx_keys = (int)round_up(env_int("BIFATTN_CTX_KEYS", (int)keys), step);
     P->ctx_row_blocks = 1;
   } else {
     // Many rows: eight-wave work-groups of 128 rows share each staged
@@ -219,8 +234,11 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true) {
   P->n_ctx_blocks = P->ctx_mode == kCtxLarge ? d.g * P->S_c * P->ctx_row_blocks : 0;
   P->n_ctx_small_blocks = P->ctx_mode == kCtxLarge ? 0 : d.g * P->S_c;
   if (d.m_d_max > 0) {
-    P->dec_keys = (int)round_up(env_int("BIFATTN_DEC_KEYS", dec_chunk_keys(units, d.m_d_max)),
-                                kTileKeys);
+    // Halves under 256 keys (two tiles per wave) don't pay: b 2, h 32, g 8,
+    // m_d 200, 12.3 us per step with chunks of 128, 11.3 with one of 256;
+    // b 20, h 8, g 4, m_d 300, 32.9 with 192, 30.3 with one chunk.
+    P->dec_keys = (int)round_up(
+        env_int("BIFATTN_DEC_KEYS", dec_chunk_keys(units, d.m_d_max, coarse ? 128 : 256)), kTileKeys);
     P->S_d = (int)ceil_div(d.m_d_max, P->dec_keys);
   } else {
     P->dec_keys = kTileKeys;
@@ -722,8 +740,22 @@ bifattn_status_t bifattn_decode_noalloc(const bifattn_dims_t* dims, const void* 
   P.scale = dims->scale != 0.f ? dims->scale : 1.0f / std::sqrt((float)dims->d);
   st = plan_splits(&P, false);
   if (st != BIFATTN_OK) return st;
-  const WorkspaceLayout L = workspace_layout(&P, false);
-  if (L.bytes > kScratchBytes) return BIFATTN_ESCRATCH;
+  WorkspaceLayout L = workspace_layout(&P, false);
+  if (L.bytes > kScratchBytes / 4) {
+    // Which problems fit is a matter of the longest chunks, which differ
+    // from the plan's by less than half the scratch.
+    bifattn_plan_s Q;
+    Q.dims = P.dims;
+    Q.scale = P.scale;
+    st = plan_splits(&Q, false, true);
+    if (st != BIFATTN_OK) return st;
+    const WorkspaceLayout Lq = workspace_layout(&Q, false);
+    if (Lq.bytes > kScratchBytes) return BIFATTN_ESCRATCH;
+    if (L.bytes > kScratchBytes) {
+      P = Q;
+      L = Lq;
+    }
+  }
   if (hipGetDevice(&P.device) != hipSuccess) {
     (void)hipGetLastError();
     return BIFATTN_EHIP;

@@ -1,0 +1,96 @@
+"""Work splits of few-row plans that leave part of the GPU idle: shorter
+context and decode chunks, against the oracle; and which problems the
+allocation-free entry point takes, which does not depend on them."""
+import ctypes
+import random
+
+import pytest
+
+import oracle
+import paper_2403_08845_amd as bif
+import workloads
+
+from .parity import assert_parity
+
+
+def _ceil(a, b):
+    return -(-a // b)
+
+
+def _coarse_bytes(b, h, g, d, m_c, m_d):
+    """Workspace of the longest few-row chunks (context 1024..2048 keys, a
+    quarter of the context; decode chunks halved down to 128 keys)."""
+    p, M, units = h // g, b * (h // g), b * g
+    assert M <= 64
+    ctx = min(2048, max(1024, 128 * _ceil(_ceil(m_c, 4), 128)))
+    dec = min(1024, max(128, 128 * _ceil(m_d, 128)))
+    while dec > 128 and units * _ceil(m_d, dec) < 128:
+        dec //= 2
+    rows = (g * _ceil(m_c, ctx) * M, units * _ceil(m_d, 32 * _ceil(dec, 32)) * 4 * p)
+    off = 0
+    for r in rows:
+        for size in (r * d * 4, r * 8):
+            off = 256 * _ceil(off + size, 256)
+    return 256 * _ceil(off + 4, 256)
+
+
+def test_noalloc_takes_the_problems_whose_longest_chunks_fit():
+    L = bif.lib()
+    rng = random.Random(4)
+    fake = ctypes.c_void_p(256)
+    seen = {True: 0, False: 0}
+    for _ in range(4000):
+        p = rng.choice((1, 2, 4, 8))
+        b = rng.randint(1, 64 // p)
+        g = rng.randint(1, 1200)
+        d = rng.choice((64, 128))
+        m_c = rng.choice((rng.randint(1, 300), rng.randint(300, 9000)))
+        m_d = rng.randint(1, 1100)
+        if m_c + m_d > 60000:
+            continue
+        need = _coarse_bytes(b, g * p, g, d, m_c, m_d)
+        if not (40 << 20) < need < (90 << 20):
+            continue
+        dims = bif.noalloc_dims(b, g * p, g, d, m_c, m_d, path="bifurcated")
+        # an unaligned pointer: a problem that fits goes no further than the argument checks
+        st = L.bifattn_decode_noalloc(ctypes.byref(dims), ctypes.c_void_p(8), fake, fake, fake,
+                                      fake, fake, None, None, fake, None)
+        fits = need <= bif.NOALLOC_SCRATCH_BYTES
+        assert (st == bif.ESCRATCH) == (not fits), (b, g, p, d, m_c, m_d, need, st)
+        seen[fits] += 1
+    assert min(seen.values()) > 20, seen
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [
+    # b, h, g, d, m_c, m_d, n, kv
+    (2, 32, 8, 128, 3001, 200, 1, "bf16"),   # 256-key chunks, the last one short
+    (3, 16, 4, 64, 257, 40, 2, "bf16"),      # one key in the second chunk
+    (1, 4, 1, 128, 1, 1, 1, "bf16"),         # the smallest
+    (20, 8, 4, 128, 5000, 300, 1, "int8"),   # 256-key chunks, one decode chunk of 384
+    (16, 32, 8, 128, 6000, 1000, 1, "bf16"),  # M = 64, two decode chunks
+    (4, 40, 40, 128, 1300, 600, 1, "int4"),
+    (9, 32, 32, 64, 2100, 30, 1, "fp8_e4m3"),
+], ids=lambda c: "b%d_h%d_g%d_d%d_mc%d_md%d_n%d_%s" % c)
+def test_short_chunks_match_the_oracle(case):
+    import torch
+    from .gpu_util import to_device
+    b, h, g, d, m_c, m_d, n, kv = case
+    x = workloads.make_inputs(b, h, g, d, m_c, m_d, seed=1900 + m_c, ragged=True, n=n, kv=kv,
+                              poison_tail=True)
+    dev = to_device(x)
+    outs = []
+    with bif.Plan(b, h, g, d, m_c, m_d, n=n, kv=kv, path="bifurcated") as plan:
+        info = plan.info()
+        print(f"[case] {case} {info}", flush=True)
+        assert info["ctx_kernel"] == 0 and info["ctx_keys_per_block"] <= 1024
+        for call in (lambda *a: bif.bifattn_decode_scaled(plan, *a),
+                     lambda *a: bif.bifattn_decode_noalloc(
+                         bif.noalloc_dims(b, h, g, d, m_c, m_d, n=n, kv=kv, path="bifurcated"), *a)):
+            out = torch.full(tuple(x["q"].shape), float("nan"), dtype=torch.float32, device="cuda")
+            call(dev["q"], dev["Kc"], dev["Vc"], dev["Kd"], dev["Vd"], dev["lens"],
+                 dev["k_scale"], dev["v_scale"], out)
+            torch.cuda.synchronize()
+            outs.append(out)
+    assert torch.equal(*outs)
+    assert_parity(outs[0].cpu().double().numpy(), oracle.attention(**x), str(case), x=x)
