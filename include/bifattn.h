@@ -138,7 +138,9 @@ typedef struct {
   int32_t ctx_kernel;         /* context work-groups: 0 in the partial launch (few rows per
                                  group, or none), 1 many-row kernel of 16-row waves, 2 many-row
                                  32x32 MFMA kernel of 32-row waves */
-  int32_t side_stream;        /* 1 when the decode launch runs on the plan's side stream */
+  int32_t side_stream;        /* 1 when the decode work-groups run beside the many-row context
+                                 work-groups: in their launch (fused = 1), or on the plan's side
+                                 stream */
 } bifattn_plan_info_t;
 
 /* Kernels a plan launches; used to select what bifattn_plan_set_timing times. */
@@ -188,8 +190,9 @@ bifattn_status_t bifattn_plan_get_info(bifattn_plan_t plan, bifattn_plan_info_t 
  * one group once and applies it to all b*p query rows of the group; (b)
  * decode partials: per sample and group over its own Kd/Vd; (c) the combine,
  * which merges the (max, sum, weighted-value) partials of both parts into
- * `out`. With many query rows per group (b*(h/g)*n > 64) and a decode cache
- * of 16 MiB or more, (b) runs on a stream the plan owns, beside (a), and
+ * `out`. (a) and (b) are one launch, except with many query rows per group
+ * (b*(h/g)*n > 64) where d = 64 or (h/g)*n > 32: there (b) follows (a), or,
+ * with a large decode cache, runs on a stream the plan owns, beside (a), and
  * `stream` waits for it before (c). On a plan whose path is BIFATTN_PATH_STANDARD it enqueues one
  * launch instead: per (sample, group), the context rows then the decode
  * rows in one softmax, written to `out`. Kd, Vd and decode_lens may be NULL only when m_d_max == 0.
@@ -303,8 +306,8 @@ bifattn_status_t bifattn_plan_read_timing(bifattn_plan_t plan, int32_t *calls, d
  * bifattn_decode_scaled for callers that cannot allocate device memory:
  * code under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation. It takes the dimensions instead of a plan (creating a plan
- * allocates), computes the same work split on the host (the decode launch
- * always on `stream`, never on a side stream), and keeps its partials and
+ * allocates), computes the same work split on the host (every launch on
+ * `stream`, never on a side stream), and keeps its partials and
  * status word in a fixed scratch buffer of BIFATTN_NOALLOC_SCRATCH_BYTES
  * (64 MiB) that the library holds on each GPU from its load to the end of
  * the process. It calls no allocator, creates no stream or event, and

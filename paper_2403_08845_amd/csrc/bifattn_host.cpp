@@ -26,8 +26,9 @@ struct bifattn_plan_s {
   int ctx_wide = 0;  // many-row path: waves per work-group of the 32x32 kernel, or 0
   int dec_keys = 0, S_d = 0, n_dec_blocks = 0;
   int rep_keys = 0, S_r = 0, n_rep_blocks = 0;
-  int fused = 1;
-  int fork = 0;        // many-row path: decode launch on a side stream beside the context kernel
+  int fused = 1;       // context and decode work-groups in one launch
+  int fork = 0;        // many-row path: decode work-groups beside the context ones (in their
+                       // launch when fused, else on the side stream)
   // The plan's own stream (non-blocking, default priority): the workspace is
   // allocated and freed in its order (stream-ordered allocator, so that
   // freeing it does not synchronise the device) and, on many-row plans with
@@ -129,6 +130,46 @@ int ck_step(int key_step, int64_t m_c, int64_t splits) {
   return key_step == 64 && ceil_div(m_c, splits) >= 1024 ? 128 : key_step;
 }
 
+// Key splits of a launch that holds the 32x32 context work-groups and the
+// decode work-groups. More splits shorten the context work-groups, but each
+// adds a partial of every query row for the combine, and context work-groups
+// beyond what the decode ones leave of the GPU run behind others. Estimated
+// from times measured over 22 MHA, GQA and MQA layers (100 to 4096 rows per
+// group, 1k to 32k keys), where the choice is within 1.4% of the best number
+// of splits on average and 11% at worst:
+//   context work-group: 9.8 us + 24 ns per key (eight waves, 256 rows) or
+//     16 ns (four waves, 128 rows), up to a third more as more than five
+//     eighths of the CUs run them (the clock gives way);
+//   decode work-group: 2.6 us + 2.1 us per 128 keys;
+//   combine: its partials at 3.2 TB/s.
+int64_t fused_splits(const bifattn_plan_s* P, int64_t per_split, int64_t rows) {
+  const bifattn_dims_t& d = P->dims;
+  const bool eight = P->ctx_wide == 8;
+  const int slots = eight ? kCUs : 2 * kCUs;
+  const int64_t S_d = P->S_d;
+  const int64_t dec_wgs = ceil_div((int64_t)d.b * d.g * S_d, P->ctx_wide / kWaves);
+  const double td = 2.6 + 2.1 * (double)ceil_div(std::min<int64_t>(P->dec_keys, d.m_d_max), 128);
+  const int64_t most = std::max<int64_t>(1, std::min(ceil_div(d.m_c, 128), 2 * slots / per_split));
+  double best = 0.0;
+  int64_t choice = 1;
+  for (int64_t S = 1; S <= most; S += 1 + S / 16) {
+    const int64_t keys = round_up(ceil_div(d.m_c, S), ck_step(64, d.m_c, S));
+    const int64_t wgs = per_split * ceil_div(d.m_c, keys);
+    const double busy = 1.0 + 0.32 * (double)std::max<int64_t>(0, std::min<int64_t>(wgs, kCUs) - 160) / 96;
+    const double tc = 9.8 + (eight ? 0.024 : 0.016) * (double)keys * busy;
+    double t;
+    if (wgs >= slots) {
+      t = (double)ceil_div(wgs, slots) * tc + (double)dec_wgs * td / slots;
+    } else {
+      const double beside = (double)ceil_div(dec_wgs, slots - wgs) * td;
+      t = std::max(tc, beside <= tc + td ? beside : ((double)wgs * tc + (double)dec_wgs * td) / slots + 0.5 * td);
+    }
+    t += (double)(ceil_div(d.m_c, keys) + 4 * S_d) * d.g * rows * (d.d * 4 + 16) / 3.2e6;
+    if (S == 1 || t < best) best = t, choice = S;
+  }
+  return choice;
+}
+
 // Keys one replicated-ablation work-group reads: `start` by default, halved
 // (down to 128) while fewer than two work-groups per CU would exist.
 int seq_keys(int64_t units, int64_t rows, int start) {
@@ -151,6 +192,17 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
   P->dec_tiles = P->p <= 16 ? 1 : (P->p <= 32 ? 2 : 4);
   const int64_t M = P->M;
   const int64_t units = (int64_t)d.b * d.g;
+  if (d.m_d_max > 0) {
+    // Halves under 256 keys (two tiles per wave) don't pay: b 2, h 32, g 8,
+    // m_d 200, 12.3 us per step with chunks of 128, 11.3 with one of 256;
+    // b 20, h 8, g 4, m_d 300, 32.9 with 192, 30.3 with one chunk.
+    P->dec_keys = (int)round_up(
+        env_int("BIFATTN_DEC_KEYS", dec_chunk_keys(units, d.m_d_max, coarse ? 128 : 256)), kTileKeys);
+    P->S_d = (int)ceil_div(d.m_d_max, P->dec_keys);
+  } else {
+    P->dec_keys = kTileKeys;
+    P->S_d = 0;
+  }
   if (M <= 64) {
     // Few rows per group: S_c work-groups per group, interleaved over the
     // group's tiles. Where the step fills the GPU, about four of them, each
@@ -176,56 +228,48 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
     P->ctx_keys = (int)round_up(env_int("BIFATTN_CTX_KEYS", (int)keys), step);
     P->ctx_row_blocks = 1;
   } else {
-    // Many rows: eight-wave work-groups of 128 rows share each staged
-    // K_c/V_c tile; about two work-groups per CU (four waves per SIMD).
-    // With a large decode part (16 MiB of decode KV or more) the decode
-    // launch runs on a side stream beside the context kernel, which then
-    // takes about one work-group per CU and leaves the other slot to the
-    // decode work-groups (the context part is bound by the matrix cores, the
-    // decode part by HBM). BIFATTN_FORK=0/1 forces it off/on.
-    P->ctx_mode = kCtxLarge;
+    // Many rows. d = 128 takes the 32x32 MFMA kernel (work-groups of eight
+    // waves of 32 rows, one per CU, from 256 rows per group, else of four, two
+    // per CU), d = 64 the kernel of 16-row waves (eight per work-group, two
+    // work-groups per CU). BIFATTN_CTX_WIDE=0/1 forces either for d = 128.
     //
-    // The decode launch goes to the plan's side stream, beside the context
-    // kernel (eight 16-row waves per work-group, at two per CU, leaving room
-    // for decode work-groups), when the decode part is large (16 MiB or more)
-    // and comparable to the context part: its HBM time at ~5 TB/s above half
-    // the context's matrix time at ~1 PFLOP/s. Otherwise both parts run one
-    // after the other on the call's stream, and d = 128 takes the 32x32 MFMA
-    // context kernel (work-groups of eight waves of 32 rows, one per CU, from
-    // 256 rows per group, else of four, two per CU), which fills its CUs'
-    // registers and LDS and so leaves no room for decode work beside it.
-    // With the side stream, 256 or more rows per group still take the 32x32
-    // kernel, on a grid of five eighths of the CUs: the decode work-groups
-    // run on the rest (measured on the ragged GQA workload: 265 vs 276 us per
-    // step with the 16x16 kernel beside the decode launch; 160 work-groups
-    // 234-236 vs 240-241 us for 192, 243 for 144, 258 for 208: the two parts
-    // take about as long either way, and fewer key splits leave the combine
-    // fewer partials). 128 to 255 rows per group take its four-wave form on
-    // about one work-group per CU, the other slot of each CU left to decode
-    // work-groups (4 draft tokens: 89.8-89.9 vs 92.7-92.9 us for the 16x16
-    // kernel; 128-192 or 320 work-groups 92-94 us); fewer rows keep the 16x16
-    // kernel.
-    // BIFATTN_FORK=0/1 and BIFATTN_CTX_WIDE=0/1 force either choice (d = 64
-    // always takes the kernel of 16-row waves).
+    // The context part is bound by the matrix cores and the decode part by
+    // HBM, so they run beside each other. The 32x32 kernel's launch holds the
+    // decode work-groups after the context ones (units of at most 32 query
+    // rows: more need registers that two waves per SIMD don't leave); against
+    // a second launch behind it or on a side stream (us per step): MQA, 128
+    // samples over 16k, 64.2 -> 53.7-57; 4 draft tokens 89-95 -> 81.6; b 40,
+    // h 32, g 8, m_c 3000 31.6 -> 19.5. Otherwise a large decode part (16 MiB
+    // or more, its HBM time at ~5 TB/s above half the context's matrix time
+    // at ~1 PFLOP/s) goes to the plan's side stream, and a small one follows
+    // the context kernel. BIFATTN_FORK=0/1 forces the parts behind or beside
+    // each other.
+    P->ctx_mode = kCtxLarge;
     const double dec_bytes = 2.0 * d.b * d.g * (double)d.m_d_max * kv_row_bytes(d.d, d.kv_type);
     const double ctx_flops = 4.0 * d.h * P->ntok * d.d * (double)d.b * d.m_c;
-    const int fork_env = env_switch("BIFATTN_FORK");
-    const bool big_decode = dec_bytes >= 16.0 * (1 << 20) && dec_bytes / 5e12 > 0.5 * ctx_flops / 1e15;
-    P->fork = allow_fork && d.m_d_max > 0 && (fork_env == -1 ? big_decode : fork_env == 1);
+    const int fork_env = coarse ? 0 : env_switch("BIFATTN_FORK");
     const int wide_env = env_switch("BIFATTN_CTX_WIDE");
-    const bool wide = d.d == 128 && (wide_env == -1 ? (!P->fork || M >= 128) : wide_env == 1);
+    const bool one_launch = !coarse && d.d == 128 && P->dec_tiles <= 2 && wide_env != 0;
+    const bool big_decode = dec_bytes >= 16.0 * (1 << 20) && dec_bytes / 5e12 > 0.5 * ctx_flops / 1e15;
+    P->fork = (allow_fork || one_launch) && d.m_d_max > 0 &&
+              (fork_env == -1 ? one_launch || big_decode : fork_env == 1);
+    P->fused = one_launch && P->fork;
+    const bool wide = d.d == 128 && (wide_env == -1 ? one_launch || !P->fork || M >= 128 : wide_env == 1);
     P->ctx_wide = wide ? (M >= 256 ? 8 : 4) : 0;
     const int block_rows = wide ? 32 * P->ctx_wide : kLargeRowsPerBlock;
     const int key_step = wide ? 64 : kTileKeys;  // keys per stage of the kernel's loop
     P->ctx_row_blocks = (int)ceil_div(M, block_rows);
-    // About one work-group per CU for eight-wave work-groups, two for
-    // four-wave ones; with the side stream, one per CU for the 16x16 kernel
-    // (the decode work-groups take the other slot of each CU) and for the
-    // four-wave 32x32 kernel, and five eighths of the CUs for the eight-wave
-    // 32x32 kernel (the decode work-groups take the rest).
-    const int per_cu = P->ctx_wide == 8 ? 1 : 2;
-    const int target = P->fork ? (P->ctx_wide == 8 ? kCUs * 5 / 8 : kCUs) : per_cu * kCUs;
-    int64_t splits = ceil_div(env_int("BIFATTN_CTX_WGS", target), (int64_t)d.g * P->ctx_row_blocks);
+    const int64_t per_split = (int64_t)d.g * P->ctx_row_blocks;  // work-groups of one key split
+    // With the decode work-groups in a launch of their own: about one
+    // work-group per CU for eight-wave work-groups, two for four-wave ones;
+    // beside the side stream, one per CU (five eighths of that with eight
+    // waves of 32 rows: the decode work-groups take the rest).
+    const int target = P->fork ? (P->ctx_wide == 8 ? kCUs * 5 / 8 : kCUs)
+                               : (P->ctx_wide == 8 ? kCUs : 2 * kCUs);
+    const int wgs = env_int("BIFATTN_CTX_WGS", 0);
+    int64_t splits = wgs > 0      ? ceil_div(wgs, per_split)
+                     : one_launch ? fused_splits(P, per_split, M)
+                                  : ceil_div(target, per_split);
     if (splits < 1) splits = 1;
     const int64_t ck = round_up(ceil_div(d.m_c, splits), ck_step(key_step, d.m_c, splits));
     P->ctx_keys = (int)round_up(env_int("BIFATTN_CTX_KEYS", (int)ck), key_step);
@@ -233,17 +277,6 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
   P->S_c = (int)ceil_div(d.m_c, P->ctx_keys);
   P->n_ctx_blocks = P->ctx_mode == kCtxLarge ? d.g * P->S_c * P->ctx_row_blocks : 0;
   P->n_ctx_small_blocks = P->ctx_mode == kCtxLarge ? 0 : d.g * P->S_c;
-  if (d.m_d_max > 0) {
-    // Halves under 256 keys (two tiles per wave) don't pay: b 2, h 32, g 8,
-    // m_d 200, 12.3 us per step with chunks of 128, 11.3 with one of 256;
-    // b 20, h 8, g 4, m_d 300, 32.9 with 192, 30.3 with one chunk.
-    P->dec_keys = (int)round_up(
-        env_int("BIFATTN_DEC_KEYS", dec_chunk_keys(units, d.m_d_max, coarse ? 128 : 256)), kTileKeys);
-    P->S_d = (int)ceil_div(d.m_d_max, P->dec_keys);
-  } else {
-    P->dec_keys = kTileKeys;
-    P->S_d = 0;
-  }
   P->n_dec_blocks = (int)(units * P->S_d);
   const int64_t rep_rows = (int64_t)d.m_c + d.m_d_max;
   P->rep_keys = (int)round_up(env_int("BIFATTN_REP_KEYS", seq_keys(units, rep_rows, 1024)),
@@ -252,10 +285,8 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
   P->n_rep_blocks = (int)(units * P->S_r);
   // Few-row context and decode work-groups share one launch (the context
   // part then overlaps the decode part's streaming); BIFATTN_LAUNCH=2 splits
-  // them into two launches. The many-row context path has a kernel of its
-  // own (eight-wave work-groups), launched before the decode work-groups.
-  const int launch = env_int("BIFATTN_LAUNCH", 1);
-  P->fused = launch == 1 && P->ctx_mode != kCtxLarge ? 1 : 0;
+  // them into two launches.
+  if (P->ctx_mode != kCtxLarge) P->fused = env_int("BIFATTN_LAUNCH", 1) == 1;
   // The workload-based switch: the standard path reads the context once per
   // sample but needs one launch and no partials. It wins while every unit is
   // resident in one round of work-groups (b*g <= 512), has at most two query
@@ -565,7 +596,7 @@ bifattn_status_t bifattn_plan_create(const bifattn_dims_t* dims, bifattn_plan_t*
     release_plan(P);
     return BIFATTN_EHIP;
   }
-  if (P->fork) {
+  if (P->fork && !P->fused) {
     if (hipEventCreateWithFlags(&P->fork_ev, kOrderEventFlags) != hipSuccess ||
         hipEventCreateWithFlags(&P->join_ev, kOrderEventFlags) != hipSuccess) {
       (void)hipGetLastError();
@@ -653,7 +684,14 @@ bifattn_status_t decode_impl(bifattn_plan_s* P, const void* q, const void* Kc, c
   // Two launches: the first carries the start event and the second the end
   // event, unless there are no decode work-groups (then the first carries both).
   const bool two = P->n_dec_blocks > 0;
-  if (P->ctx_mode == kCtxLarge && P->fork && two) {
+  if (P->ctx_mode == kCtxLarge && P->fused && two) {
+    // One launch holds the context and the decode work-groups: each section
+    // times it.
+    K.n_ctx_blocks = P->n_ctx_blocks;
+    K.n_dec_blocks = P->n_dec_blocks;
+    e = launch_ctx_large(K, P->dims.d, kv, P->dec_tiles, stream,
+                         ev(ev(part.both(), ctxs.both()), decs.both()));
+  } else if (P->ctx_mode == kCtxLarge && P->fork && two) {
     // The decode work-groups on the side stream, beside the many-row context
     // kernel; the call's stream waits for them before the combine. The timed
     // section is the call's stream from before the fork to after the join.
@@ -665,7 +703,7 @@ bifattn_status_t decode_impl(bifattn_plan_s* P, const void* q, const void* Kc, c
       return BIFATTN_EHIP;
     e = launch_partials(Kd, P->dims.d, kv, kCtxNone, P->dec_tiles, P->side, decs.both());
     K.n_ctx_blocks = P->n_ctx_blocks;
-    if (e == hipSuccess) e = launch_ctx_large(K, P->dims.d, kv, stream, ctxs.both());
+    if (e == hipSuccess) e = launch_ctx_large(K, P->dims.d, kv, P->dec_tiles, stream, ctxs.both());
     if (e == hipSuccess && (hipEventRecord(P->join_ev, P->side) != hipSuccess ||
                             hipStreamWaitEvent(stream, P->join_ev, 0) != hipSuccess))
       e = hipErrorUnknown;
@@ -674,7 +712,7 @@ bifattn_status_t decode_impl(bifattn_plan_s* P, const void* q, const void* Kc, c
   } else if (P->ctx_mode == kCtxLarge) {
     // The many-row context kernel, then the decode work-groups.
     K.n_ctx_blocks = P->n_ctx_blocks;
-    e = launch_ctx_large(K, P->dims.d, kv, stream,
+    e = launch_ctx_large(K, P->dims.d, kv, P->dec_tiles, stream,
                          ev(two ? part.first() : part.both(), ctxs.both()));
     K.n_ctx_blocks = 0;
     K.n_dec_blocks = P->n_dec_blocks;
@@ -741,9 +779,9 @@ bifattn_status_t bifattn_decode_noalloc(const bifattn_dims_t* dims, const void* 
   st = plan_splits(&P, false);
   if (st != BIFATTN_OK) return st;
   WorkspaceLayout L = workspace_layout(&P, false);
-  if (L.bytes > kScratchBytes / 4) {
+  if (L.bytes > kScratchBytes / 16) {
     // Which problems fit is a matter of the longest chunks, which differ
-    // from the plan's by less than half the scratch.
+    // from these by well under that factor.
     bifattn_plan_s Q;
     Q.dims = P.dims;
     Q.scale = P.scale;

@@ -149,8 +149,10 @@ constexpr size_t kScratchBytes = size_t(64) << 20;
 // that device current; later calls return the cached address).
 hipError_t scratch_address(int device, void** ptr);
 
-// Launch the many-row context kernel over n_ctx_blocks work-groups.
-hipError_t launch_ctx_large(const PartialsParams& P, int d, int kv, hipStream_t stream,
-                            const LaunchEvents& ev = {});
+// Launch the many-row context kernel over n_ctx_blocks work-groups; the 32x32
+// kernel's launch also holds the n_dec_blocks decode work-groups (dec_tiles
+// query tiles, at most 2).
+hipError_t launch_ctx_large(const PartialsParams& P, int d, int kv, int dec_tiles,
+                            hipStream_t stream, const LaunchEvents& ev = {});
 
 }  // namespace bifattn

@@ -1181,8 +1181,11 @@ __device__ __forceinline__ void read_vt_block(uint32_t a, u32x2 (&w)[16]) {
 #undef BIFATTN_TR
 }
 
+// Bytes of LDS of a context work-group's stage buffers.
+constexpr int wide_stage_bytes(int NB, int SK) { return NB * SK * (wide::KROW + wide::VROW); }
+
 template <int NW, int NB, int SK, typename KV>
-__device__ __forceinline__ void ctx_wide_body(const PartialsParams& P) {
+__device__ __forceinline__ void ctx_wide_block(const PartialsParams& P, unsigned char* lds) {
   using wide::D;
   using wide::RB;
   using wide::KSTEPS;
@@ -1199,7 +1202,6 @@ __device__ __forceinline__ void ctx_wide_body(const PartialsParams& P) {
   constexpr int LPW = (LOADS + NW - 1) / NW;   // loads per wave per stage (the last ones fewer)
   constexpr int FULL = LOADS - (LPW - 1) * NW;  // waves with LPW loads; the rest have LPW - 1
   static_assert(STAGE % 1024 == 0 && KAREA % 1024 == 0, "stage areas are whole loads");
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[NB * STAGE];
   const int blk = xcd_logical(blockIdx.x, P.g * P.S_c, P.ctx_row_blocks);
   const int rb = blk % P.ctx_row_blocks;
   const int sg = blk / P.ctx_row_blocks;
@@ -1242,8 +1244,10 @@ __device__ __forceinline__ void ctx_wide_body(const PartialsParams& P) {
       if (u < nload) {
         const int i = wave + NW * u;  // wave-uniform
         lds_void* dst = (lds_void*)(lds + buf * STAGE + i * 1024);
+#if defined(__HIP_DEVICE_COMPILE__)  // the host pass does not know the 16-byte form
         __builtin_amdgcn_raw_ptr_buffer_load_lds(i < KAREA / 1024 ? rk : rv, dst, 16,
                                                  boff(loff[u]), 0, 0, 0);
+#endif
       }
     }
   };
@@ -1462,13 +1466,34 @@ __device__ __forceinline__ void ctx_wide_body(const PartialsParams& P) {
   }
 }
 
-template <int NW, int NB, int SK, typename KV>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void
-ctx_wide_kernel(PartialsParams P) {
-  ctx_wide_body<NW, NB, SK, KV>(P);
+// Grid: n_ctx_blocks context work-groups, then one work-group for every
+// NW / 4 of the n_dec_blocks decode work-groups, whose waves are independent.
+template <int NW, int NB, int SK, typename KV, int NTD>
+__device__ __forceinline__ void ctx_wide_body(const PartialsParams& P) {
+  constexpr int D = wide::D;
+  constexpr int QB = NTD * (D / 32) * 64 * 16;  // bytes of a decode wave's Q^T operands
+  constexpr int KB = kTileKeys * D * 2;         // and of its K tile
+  constexpr int LDS = cmax(wide_stage_bytes(NB, SK), NW * (QB + KB));
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS];
+  const int bid = blockIdx.x;
+  if (bid < P.n_ctx_blocks) {
+    ctx_wide_block<NW, NB, SK, KV>(P, lds);
+    return;
+  }
+  const int lane = threadIdx.x & 63, wave = wave_id();
+  const int blk = (bid - P.n_ctx_blocks) * (NW / kWaves) + wave / kWaves;
+  if (blk < P.n_dec_blocks) {
+    unsigned char* mine = lds + wave * (QB + KB);
+    decode_block<D, NTD, KV>(P, blk, wave % kWaves, lane, reinterpret_cast<u32x4*>(mine),
+                             reinterpret_cast<u32x4*>(mine + QB));
+  }
 }
 
-
+template <int NW, int NB, int SK, typename KV, int NTD>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void
+ctx_wide_kernel(PartialsParams P) {
+  ctx_wide_body<NW, NB, SK, KV, NTD>(P);
+}
 
 // Grid: n_ctx_small_blocks work-groups of the few-row context path, then
 // n_dec_blocks decode work-groups (the many-row context path has a kernel of
@@ -1694,7 +1719,7 @@ hipError_t launch_standard_d(const PartialsParams& P, int kv, int tiles, hipStre
   }
 }
 
-template <typename KV>
+template <typename KV, int NTD>
 hipError_t launch_ctx_wide_kv(const PartialsParams& P, hipStream_t stream,
                               const LaunchEvents& ev) {
   constexpr bool kDirect = KV::BITS == 16;
@@ -1702,13 +1727,28 @@ hipError_t launch_ctx_wide_kv(const PartialsParams& P, hipStream_t stream,
   // stages, measured 3-5% faster); chunks of a multiple of 64 keys (three
   // 64-key stages in LDS for bf16, two for code caches, which stage a
   // third in registers)
+  const int per = P.ctx_wide / kWaves;  // decode work-groups in one of the launch's
+  if (per < 1) return hipErrorInvalidValue;
+  const int grid = P.n_ctx_blocks + (P.n_dec_blocks + per - 1) / per;
   if (P.ctx_wide == 8) {
     if (P.ctx_keys % 128 == 0)
-      return launch(ctx_wide_kernel<8, 2, 128, KV>, P.n_ctx_blocks, 512, stream, ev, P);
-    return launch(ctx_wide_kernel<8, kDirect ? 3 : 2, 64, KV>, P.n_ctx_blocks, 512, stream, ev, P);
+      return launch(ctx_wide_kernel<8, 2, 128, KV, NTD>, grid, 512, stream, ev, P);
+    return launch(ctx_wide_kernel<8, kDirect ? 3 : 2, 64, KV, NTD>, grid, 512, stream, ev, P);
   }
-  if (P.ctx_wide == 4) return launch(ctx_wide_kernel<4, 2, 64, KV>, P.n_ctx_blocks, 256, stream, ev, P);
+  if (P.ctx_wide == 4) return launch(ctx_wide_kernel<4, 2, 64, KV, NTD>, grid, 256, stream, ev, P);
   return hipErrorInvalidValue;
+}
+
+template <int NTD>
+hipError_t launch_ctx_wide(const PartialsParams& P, int kv, hipStream_t stream,
+                           const LaunchEvents& ev) {
+  switch (kv) {
+    case kKvBf16: return launch_ctx_wide_kv<KvBf16, NTD>(P, stream, ev);
+    case kKvFp8: return launch_ctx_wide_kv<KvFp8, NTD>(P, stream, ev);
+    case kKvInt8: return launch_ctx_wide_kv<KvInt8, NTD>(P, stream, ev);
+    case kKvInt4: return launch_ctx_wide_kv<KvInt4, NTD>(P, stream, ev);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 template <int D>
@@ -1795,19 +1835,16 @@ hipError_t scratch_address(int device, void** ptr) {
   return hipSuccess;
 }
 
-hipError_t launch_ctx_large(const PartialsParams& P, int d, int kv, hipStream_t stream,
-                            const LaunchEvents& ev) {
+hipError_t launch_ctx_large(const PartialsParams& P, int d, int kv, int dec_tiles,
+                            hipStream_t stream, const LaunchEvents& ev) {
   if (P.n_ctx_blocks == 0) return hipSuccess;
   if (P.ctx_wide) {
     if (d != 128) return hipErrorInvalidValue;
-    switch (kv) {
-      case kKvBf16: return launch_ctx_wide_kv<KvBf16>(P, stream, ev);
-      case kKvFp8: return launch_ctx_wide_kv<KvFp8>(P, stream, ev);
-      case kKvInt8: return launch_ctx_wide_kv<KvInt8>(P, stream, ev);
-      case kKvInt4: return launch_ctx_wide_kv<KvInt4>(P, stream, ev);
-      default: return hipErrorInvalidValue;
-    }
+    if (P.n_dec_blocks > 0 && dec_tiles > 2) return hipErrorInvalidValue;
+    return P.n_dec_blocks > 0 && dec_tiles == 2 ? launch_ctx_wide<2>(P, kv, stream, ev)
+                                                : launch_ctx_wide<1>(P, kv, stream, ev);
   }
+  if (P.n_dec_blocks > 0) return hipErrorInvalidValue;
   if (d == 128) return launch_ctx_large_d<128>(P, kv, stream, ev);
   if (d == 64) return launch_ctx_large_d<64>(P, kv, stream, ev);
   return hipErrorInvalidValue;

@@ -19,7 +19,7 @@ hipError_t launch_standard(const PartialsParams&, int, int, int, hipStream_t,
                            const LaunchEvents&) {
   return hipErrorNoDevice;
 }
-hipError_t launch_ctx_large(const PartialsParams&, int, int, hipStream_t, const LaunchEvents&) {
+hipError_t launch_ctx_large(const PartialsParams&, int, int, int, hipStream_t, const LaunchEvents&) {
   return hipErrorNoDevice;
 }
 hipError_t scratch_address(int, void**) { return hipErrorNoDevice; }

@@ -94,3 +94,46 @@ def test_short_chunks_match_the_oracle(case):
             outs.append(out)
     assert torch.equal(*outs)
     assert_parity(outs[0].cpu().double().numpy(), oracle.attention(**x), str(case), x=x)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [
+    # b, h, g, d, m_c, m_d, n, kv
+    (33, 32, 1, 128, 2000, 64, 1, "bf16"),     # two query tiles per unit, an odd work-group count
+    (17, 48, 3, 128, 777, 300, 1, "bf16"),     # 272 rows per group, one idle row block wave
+    (19, 32, 8, 128, 1500, 90, 1, "bf16"),     # 76 rows per group: four-wave work-groups
+    (33, 16, 1, 128, 900, 1100, 1, "fp8_e4m3"),  # two decode chunks
+    (13, 20, 4, 128, 640, 70, 4, "int8"),      # tokens
+    (65, 8, 8, 128, 3000, 5, 1, "int4"),       # one decode tile
+    (70, 4, 1, 128, 130, 1, 1, "bf16"),        # a second key chunk of two keys
+], ids=lambda c: "b%d_h%d_g%d_d%d_mc%d_md%d_n%d_%s" % c)
+def test_many_rows_in_one_launch_equal_two(case, monkeypatch):
+    """The decode work-groups in the 32x32 context kernel's launch: the same
+    bits as in a launch of their own, the same as without a plan, and the
+    oracle's result."""
+    import torch
+    from .gpu_util import to_device
+    b, h, g, d, m_c, m_d, n, kv = case
+    x = workloads.make_inputs(b, h, g, d, m_c, m_d, seed=2000 + m_c, ragged=True, n=n, kv=kv,
+                              poison_tail=True)
+    dev = to_device(x)
+    args = [dev[k] for k in ("q", "Kc", "Vc", "Kd", "Vd", "lens", "k_scale", "v_scale")]
+    outs = []
+
+    def run(call):
+        outs.append(torch.full(tuple(x["q"].shape), float("nan"), dtype=torch.float32, device="cuda"))
+        call(*args, outs[-1])
+        torch.cuda.synchronize()
+
+    dims = bif.noalloc_dims(b, h, g, d, m_c, m_d, n=n, kv=kv, path="bifurcated")
+    for fork in ("1", "0"):
+        monkeypatch.setenv("BIFATTN_FORK", fork)
+        with bif.Plan(b, h, g, d, m_c, m_d, n=n, kv=kv, path="bifurcated") as plan:
+            info = plan.info()
+            print(f"[case] {case} {info}", flush=True)
+            assert info["ctx_kernel"] == 2 and info["fused"] == info["side_stream"] == int(fork)
+            run(lambda *a: bif.bifattn_decode_scaled(plan, *a))
+    monkeypatch.delenv("BIFATTN_FORK")
+    run(lambda *a: bif.bifattn_decode_noalloc(dims, *a))
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    assert_parity(outs[0].cpu().double().numpy(), oracle.attention(**x), str(case), x=x)
