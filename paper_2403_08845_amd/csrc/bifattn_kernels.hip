@@ -1544,14 +1544,21 @@ constexpr bool fits_two_waves() {
 // partials (sample i, group j/p, every chunk; empty ones weigh 0) into
 // out = sum_k 2^(m_k - M) acc_k / sum_k 2^(m_k - M) l_k, M = max_k m_k.
 // Lane k first fetches the statistics of partial k (all in parallel), so the
-// weights need one wave reduction; the value rows are then summed in a fixed
-// order with their loads issued ahead in batches. The group's value scale
+// weights need one wave reduction. A value row is 16 bytes of each of D/4
+// lanes, so one load instruction reads PPL = 256/D consecutive partials' rows
+// (of the context or of the decode partials: the address is a scalar plus a
+// constant lane offset), each summed by its own lanes in a fixed order, the
+// sums added across them at the end; NL loads are issued ahead, together with
+// the statistics. Bound by the memory round trip and, on MQA and GQA, by the
+// partials' bytes. The group's value scale
 // multiplies the result (every partial of the row shares it); the first row
 // of each group checks that the group's scales are positive normal floats.
-template <int D, int BATCH>
+template <int D, int NL>
 __global__ __launch_bounds__(256) void combine_kernel(CombineParams C) {
-  constexpr int PER = D / 64;
+  constexpr int LPR = D / 4;     // lanes of a value row
+  constexpr int PPL = 64 / LPR;  // partials one load reads
   const int lane = threadIdx.x & 63, wave = wave_id();
+  const int sub = lane / LPR, col = 4 * (lane % LPR);
   const int row = blockIdx.x * 4 + wave;
   if (row >= C.b * C.h) return;
   const int i = row / C.h, j = row - i * C.h;
@@ -1570,72 +1577,69 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineParams C) {
   const int np = C.S_c + C.S_d;  // every decode wave wrote a partial (maybe empty)
   const size_t cbase = (size_t)gam * C.S_c * C.M + (size_t)i * C.p + jp;  // + k*M
   const size_t dbase = ((size_t)(i * C.g + gam) * C.S_d) * C.p + jp;      // + k*p
-  auto idx = [&](int k) -> size_t {
-    return k < C.S_c ? cbase + (size_t)k * C.M : dbase + (size_t)(k - C.S_c) * C.p;
-  };
-  auto accp = [&](int k) -> const float* {
-    return (k < C.S_c ? C.ctx_acc : C.dec_acc) + idx(k) * D + lane * PER;
-  };
-  float acc[PER];
-#pragma unroll
-  for (int e = 0; e < PER; ++e) acc[e] = 0.f;
+  const size_t coff = (size_t)sub * C.M * D + col, doff = (size_t)sub * C.p * D + col;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   float L = 0.f;
   float mx = kNegInf;
   for (int k0 = 0; k0 < np; k0 += 64) {  // running max over chunks of 64 partials
-    const int kn = min(64, np - k0);
-    // Issue the first batch of value rows together with the statistics, so
-    // a chunk of up to BATCH partials costs one memory round trip; only the
-    // rows the chunk has are loaded (kn is wave-uniform).
-    float v[BATCH][PER];
+    const int k1 = min(k0 + 64, np);
+    // The chunk's loads: nc of context partials [k0, ce), then of decode
+    // partials [d0, k1). In a last, partly filled load the spare lanes repeat
+    // the load's first partial and weigh it 0.
+    const int ce = min(k1, C.S_c), d0 = max(k0, C.S_c);
+    const int nc = k0 < ce ? (ce - k0 + PPL - 1) / PPL : 0;
+    const int nl = nc + (d0 < k1 ? (k1 - d0 + PPL - 1) / PPL : 0);
+    f32x4 v[NL];
+    auto load = [&](int l0) {
 #pragma unroll
-    for (int u = 0; u < BATCH; ++u) {
-      if (u < kn) {
-        const float* a = accp(k0 + u);
-#pragma unroll
-        for (int e = 0; e < PER; ++e) v[u][e] = a[e];
+      for (int u = 0; u < NL; ++u) {
+        const int l = l0 + u;  // wave-uniform
+        if (l < nc) {
+          const int k = k0 + l * PPL;
+          const float* a = C.ctx_acc + (cbase + (size_t)k * C.M) * D;
+          v[u] = *reinterpret_cast<const f32x4*>(a + (k + sub < ce ? coff : col));
+        } else if (l < nl) {
+          const int k = d0 + (l - nc) * PPL;
+          const float* a = C.dec_acc + (dbase + (size_t)(k - C.S_c) * C.p) * D;
+          v[u] = *reinterpret_cast<const f32x4*>(a + (k + sub < k1 ? doff : col));
+        }
       }
-    }
+    };
+    load(0);
     const int k = k0 + lane;
-    const float2 ml = k < np ? (k < C.S_c ? C.ctx_ml[idx(k)] : C.dec_ml[idx(k)])
-                             : float2{kNegInf, 0.f};
+    float2 ml = float2{kNegInf, 0.f};
+    if (k < k1)
+      ml = k < C.S_c ? C.ctx_ml[cbase + (size_t)k * C.M] : C.dec_ml[dbase + (size_t)(k - C.S_c) * C.p];
     float cm = ml.x;
     cm = wave_max(cm);
     const float mnew = fmaxf(mx, cm);
     const float base = mnew == kNegInf ? 0.f : mnew;
     const float rescale = exp2_fast(mx - base);  // 0 on the first chunk
     L *= rescale;
-#pragma unroll
-    for (int e = 0; e < PER; ++e) acc[e] *= rescale;
+    acc *= rescale;
     mx = mnew;
     const float w = exp2_fast(ml.x - base);      // 0 for padding lanes
     float lw = w * ml.y;
     lw = wave_sum(lw);
     L += lw;
-    for (int kb = 0; kb < kn; kb += BATCH) {
-      if (kb > 0) {
+    for (int l0 = 0; l0 < nl; l0 += NL) {
+      if (l0 > 0) load(l0);
 #pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-          if (kb + u < kn) {
-            const float* a = accp(k0 + kb + u);
-#pragma unroll
-            for (int e = 0; e < PER; ++e) v[u][e] = a[e];
-          }
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < BATCH; ++u) {
-        const float wu = __shfl(w, min(kb + u, 63));
-        if (kb + u < kn) {
-#pragma unroll
-          for (int e = 0; e < PER; ++e) acc[e] += wu * v[u][e];
-        }
+      for (int u = 0; u < NL; ++u) {
+        const int l = l0 + u;
+        const int kk = (l < nc ? k0 + l * PPL : d0 + (l - nc) * PPL) + sub;
+        const float wu = __shfl(w, min(kk - k0, 63));
+        if (l < nl) acc += v[u] * (kk < (l < nc ? ce : k1) ? wu : 0.f);
       }
     }
   }
-  float* o = C.out + (size_t)row * D + lane * PER;
-  const float inv = vs / L;
 #pragma unroll
-  for (int e = 0; e < PER; ++e) o[e] = acc[e] * inv;
+  for (int e = 0; e < 4; ++e) {
+    if constexpr (PPL == 4) acc[e] = xor16_sum(acc[e]);
+    acc[e] = xor32_sum(acc[e]);
+  }
+  const float inv = vs / L;
+  if (sub == 0) *reinterpret_cast<f32x4*>(C.out + (size_t)row * D + col) = acc * inv;
 }
 
 // One launch; with events, through hipExtLaunchKernel so that they carry the
@@ -1867,17 +1871,18 @@ hipError_t launch_combine(const CombineParams& C, int d, hipStream_t stream,
                           const LaunchEvents& ev) {
   const int rows = C.b * C.h;
   const int grid = (rows + 3) / 4;
-  // One batch of value rows holds every partial of a row where it has at
-  // most 32 (one memory round trip), in the smallest of 8, 16, 32 rows.
-  const int np = C.S_c + C.S_d;
+  // The loads of a row's partials go out at once where there are at most 16
+  // (one memory round trip), in the smallest of 4, 8 and 16 registers sets.
+  const int per = 256 / d;
+  const int loads = (C.S_c + per - 1) / per + (C.S_d + per - 1) / per;
   if (d == 128)
-    return np <= 8 ? launch(combine_kernel<128, 8>, grid, 256, stream, ev, C)
-         : np <= 16 ? launch(combine_kernel<128, 16>, grid, 256, stream, ev, C)
-                    : launch(combine_kernel<128, 32>, grid, 256, stream, ev, C);
+    return loads <= 4 ? launch(combine_kernel<128, 4>, grid, 256, stream, ev, C)
+         : loads <= 8 ? launch(combine_kernel<128, 8>, grid, 256, stream, ev, C)
+                      : launch(combine_kernel<128, 16>, grid, 256, stream, ev, C);
   if (d == 64)
-    return np <= 8 ? launch(combine_kernel<64, 8>, grid, 256, stream, ev, C)
-         : np <= 16 ? launch(combine_kernel<64, 16>, grid, 256, stream, ev, C)
-                    : launch(combine_kernel<64, 32>, grid, 256, stream, ev, C);
+    return loads <= 4 ? launch(combine_kernel<64, 4>, grid, 256, stream, ev, C)
+         : loads <= 8 ? launch(combine_kernel<64, 8>, grid, 256, stream, ev, C)
+                      : launch(combine_kernel<64, 16>, grid, 256, stream, ev, C);
   return hipErrorInvalidValue;
 }
 
