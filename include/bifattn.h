@@ -191,7 +191,7 @@ bifattn_status_t bifattn_plan_get_info(bifattn_plan_t plan, bifattn_plan_info_t 
  * decode partials: per sample and group over its own Kd/Vd; (c) the combine,
  * which merges the (max, sum, weighted-value) partials of both parts into
  * `out`. (a) and (b) are one launch, except with many query rows per group
- * (b*(h/g)*n > 64) where d = 64 or (h/g)*n > 32: there (b) follows (a), or,
+ * (b*(h/g)*n > 32) where (h/g)*n > 32: there (b) follows (a), or,
  * with a large decode cache, runs on a stream the plan owns, beside (a), and
  * `stream` waits for it before (c). On a plan whose path is BIFATTN_PATH_STANDARD it enqueues one
  * launch instead: per (sample, group), the context rows then the decode

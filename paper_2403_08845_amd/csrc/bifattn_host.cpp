@@ -130,44 +130,71 @@ int ck_step(int key_step, int64_t m_c, int64_t splits) {
   return key_step == 64 && ceil_div(m_c, splits) >= 1024 ? 128 : key_step;
 }
 
-// Key splits of a launch that holds the 32x32 context work-groups and the
-// decode work-groups. More splits shorten the context work-groups, but each
-// adds a partial of every query row for the combine, and context work-groups
-// beyond what the decode ones leave of the GPU run behind others. Estimated
-// from times measured over 22 MHA, GQA and MQA layers (100 to 4096 rows per
-// group, 1k to 32k keys), where the choice is within 1.4% of the best number
-// of splits on average and 11% at worst:
-//   context work-group: 9.8 us + 24 ns per key (eight waves, 256 rows) or
-//     16 ns (four waves, 128 rows), up to a third more as more than five
+// Waves per work-group and key splits of a launch that holds the 32x32
+// context work-groups and the decode work-groups. More splits shorten the
+// context work-groups, but each adds a partial of every query row for the
+// combine, and context work-groups beyond what the decode ones leave of the
+// GPU run behind others. Eight waves (256 rows) halve the reads of a key
+// chunk and of its work-groups there is one per CU; four (two per CU) overlap
+// one's start and end with the other's products, which wins on short contexts
+// (b 16, h 16, g 4, 4 tokens, m_c 3000: 16.3 us per step, eight 19.1; MQA over
+// 16k: 61.6, eight 56.3). The choice is the least of an estimate fitted to the
+// times of 62 MHA, GQA and MQA layers (32 to 4096 rows per group, 0.5k to 32k
+// keys) at about ten splits and both widths each; it is within 1.8% of the
+// best of those on average and 10% at worst:
+//   context work-group: 4.3 us + 18 ns per key (eight waves), 3.4 us + 19 ns
+//     (four), d = 64 0.59 of that per key; a sixth more as more than five
 //     eighths of the CUs run them (the clock gives way);
-//   decode work-group: 2.6 us + 2.1 us per 128 keys;
-//   combine: its partials at 3.2 TB/s.
-int64_t fused_splits(const bifattn_plan_s* P, int64_t per_split, int64_t rows) {
+//   decode work-group: 1.8 us + 1.6 us per 128 keys (d = 64: 0.6 us);
+//   the caches at 5.8 TB/s, the partials at 2.2 TB/s, and 2.4 us for each
+//     further batch of sixteen loads of the combine.
+struct ManySplit {
+  int waves = 4;
+  int64_t splits = 1;
+};
+ManySplit many_row_split(const bifattn_plan_s* P, int64_t rows) {
   const bifattn_dims_t& d = P->dims;
-  const bool eight = P->ctx_wide == 8;
-  const int slots = eight ? kCUs : 2 * kCUs;
-  const int64_t S_d = P->S_d;
-  const int64_t dec_wgs = ceil_div((int64_t)d.b * d.g * S_d, P->ctx_wide / kWaves);
-  const double td = 2.6 + 2.1 * (double)ceil_div(std::min<int64_t>(P->dec_keys, d.m_d_max), 128);
-  const int64_t most = std::max<int64_t>(1, std::min(ceil_div(d.m_c, 128), 2 * slots / per_split));
-  double best = 0.0;
-  int64_t choice = 1;
-  for (int64_t S = 1; S <= most; S += 1 + S / 16) {
-    const int64_t keys = round_up(ceil_div(d.m_c, S), ck_step(64, d.m_c, S));
-    const int64_t wgs = per_split * ceil_div(d.m_c, keys);
-    const double busy = 1.0 + 0.32 * (double)std::max<int64_t>(0, std::min<int64_t>(wgs, kCUs) - 160) / 96;
-    const double tc = 9.8 + (eight ? 0.024 : 0.016) * (double)keys * busy;
-    double t;
-    if (wgs >= slots) {
-      t = (double)ceil_div(wgs, slots) * tc + (double)dec_wgs * td / slots;
-    } else {
-      const double beside = (double)ceil_div(dec_wgs, slots - wgs) * td;
-      t = std::max(tc, beside <= tc + td ? beside : ((double)wgs * tc + (double)dec_wgs * td) / slots + 0.5 * td);
+  const bool half = d.d == 64;
+  const int S_d = P->S_d;
+  const double rows_all = (double)d.g * rows;
+  const double td = 1.8 + (half ? 0.6 : 1.6) * (double)ceil_div(std::min(P->dec_keys, d.m_d_max), 128);
+  const double stream = 2.0 * d.g * kv_row_bytes(d.d, d.kv_type) *
+                        ((double)d.m_c + 0.75 * (double)d.b * d.m_d_max) / 5.8e6;
+  ManySplit best;
+  double least = 0.0;
+  for (int waves = 4; waves <= (rows > 128 ? 8 : 4); waves += 4) {
+    const int slots = waves == 8 ? kCUs : 2 * kCUs;
+    const int64_t per_split = (int64_t)d.g * ceil_div(rows, 32 * waves);
+    const double dec_wgs = (double)ceil_div((int64_t)d.b * d.g * S_d, waves / kWaves);
+    const double start = waves == 8 ? 4.3 : 3.4;
+    const double per_key = (waves == 8 ? 0.018 : 0.019) * (half ? 0.59 : 1.0);
+    const int64_t most = std::max<int64_t>(1, std::min(ceil_div(d.m_c, 128), 2 * slots / per_split));
+    for (int64_t S = 1; S <= most; S += 1 + S / 8) {
+      const int64_t keys = round_up(ceil_div(d.m_c, S), ck_step(64, d.m_c, S));
+      const double parts = (double)ceil_div(d.m_c, keys);
+      const double wgs = (double)per_split * parts;
+      const double busy = 1.0 + 0.15 * std::max(0.0, std::min(wgs, (double)kCUs) - 160.0) / 96.0;
+      const double tc = start + per_key * (double)keys * busy;
+      double t;
+      if (wgs >= slots) {
+        t = std::ceil(wgs / slots) * tc + dec_wgs * td / slots;
+      } else {
+        const double beside = std::ceil(dec_wgs / (slots - wgs)) * td;
+        t = std::max(tc, beside <= tc + td ? beside : (wgs * tc + dec_wgs * td) / slots + 0.5 * td);
+      }
+      const double loads = std::ceil(parts * d.d / 256) + std::ceil(4.0 * S_d * d.d / 256);
+      t = std::max(t, stream) + 0.15 * t + 2.4 * (std::ceil(loads / 16) - 1) +
+          (parts + 4 * S_d) * rows_all * (d.d * 4 + 16) / 2.2e6;
+      // of (nearly) equal ones the one with more splits: shorter work-groups
+      const bool first = waves == 4 && S == 1;
+      if (first || t < least * (waves == best.waves ? 1.005 : 1.0)) {
+        least = first ? t : std::min(least, t);
+        best.waves = waves;
+        best.splits = S;
+      }
     }
-    t += (double)(ceil_div(d.m_c, keys) + 4 * S_d) * d.g * rows * (d.d * 4 + 16) / 3.2e6;
-    if (S == 1 || t < best) best = t, choice = S;
   }
-  return choice;
+  return best;
 }
 
 // Keys one replicated-ablation work-group reads: `start` by default, halved
@@ -203,7 +230,13 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
     P->dec_keys = kTileKeys;
     P->S_d = 0;
   }
-  if (M <= 64) {
+  const int64_t quarter = round_up(ceil_div(d.m_c, 4), kWaves * kTileKeys);
+  const int64_t long_keys = std::min<int64_t>(2048, std::max<int64_t>(1024, quarter));
+  // Few rows: up to two query tiles per wave. (Four, 33 to 64 rows, leave one
+  // wave per SIMD: b 16, h 32, g 8, m_c 3001 21.6 us per step against 14.5
+  // with the many-row kernel, m_c 20000 34.5 against 29; they stay for units
+  // of more than 32 rows, whose decode part needs the same.)
+  if (M <= 32 || (M <= 64 && P->dec_tiles == 4)) {
     // Few rows per group: S_c work-groups per group, interleaved over the
     // group's tiles. Where the step fills the GPU, about four of them, each
     // with 1024..2048 keys (2-4 decode work-groups' worth): fewer, longer
@@ -218,8 +251,7 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
     // 38.0 -> 37.1 (1536 keys; 1024: 40.1).
     P->ctx_mode = M <= 16 ? kCtxSmall1 : (M <= 32 ? kCtxSmall2 : kCtxSmall4);
     constexpr int step = kWaves * kTileKeys;
-    const int64_t quarter = round_up(ceil_div(d.m_c, 4), step);
-    int64_t keys = std::min<int64_t>(2048, std::max<int64_t>(1024, quarter));
+    int64_t keys = long_keys;
     if (!coarse) {
       const int64_t all = (int64_t)d.g * d.m_c + units * d.m_d_max;  // keys of every unit
       const int64_t even = std::max<int64_t>(256, ceil_div(2 * all, 2 * kCUs));
@@ -228,10 +260,9 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
     P->ctx_keys = (int)round_up(env_int("BIFATTN_CTX_KEYS", (int)keys), step);
     P->ctx_row_blocks = 1;
   } else {
-    // Many rows. d = 128 takes the 32x32 MFMA kernel (work-groups of eight
-    // waves of 32 rows, one per CU, from 256 rows per group, else of four, two
-    // per CU), d = 64 the kernel of 16-row waves (eight per work-group, two
-    // work-groups per CU). BIFATTN_CTX_WIDE=0/1 forces either for d = 128.
+    // Many rows take the 32x32 MFMA kernel (work-groups of eight or four
+    // waves of 32 rows); d = 128 has the kernel of 16-row waves too (eight per
+    // work-group, two work-groups per CU), which BIFATTN_CTX_WIDE=0 forces.
     //
     // The context part is bound by the matrix cores and the decode part by
     // HBM, so they run beside each other. The 32x32 kernel's launch holds the
@@ -249,29 +280,40 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
     const double ctx_flops = 4.0 * d.h * P->ntok * d.d * (double)d.b * d.m_c;
     const int fork_env = coarse ? 0 : env_switch("BIFATTN_FORK");
     const int wide_env = env_switch("BIFATTN_CTX_WIDE");
-    const bool one_launch = !coarse && d.d == 128 && P->dec_tiles <= 2 && wide_env != 0;
+    const bool both = d.d == 128;  // the 16x16 kernel is built for it
+    const bool one_launch = !coarse && P->dec_tiles <= 2 && !(both && wide_env == 0);
     const bool big_decode = dec_bytes >= 16.0 * (1 << 20) && dec_bytes / 5e12 > 0.5 * ctx_flops / 1e15;
     P->fork = (allow_fork || one_launch) && d.m_d_max > 0 &&
               (fork_env == -1 ? one_launch || big_decode : fork_env == 1);
     P->fused = one_launch && P->fork;
-    const bool wide = d.d == 128 && (wide_env == -1 ? one_launch || !P->fork || M >= 128 : wide_env == 1);
-    P->ctx_wide = wide ? (M >= 256 ? 8 : 4) : 0;
-    const int block_rows = wide ? 32 * P->ctx_wide : kLargeRowsPerBlock;
-    const int key_step = wide ? 64 : kTileKeys;  // keys per stage of the kernel's loop
-    P->ctx_row_blocks = (int)ceil_div(M, block_rows);
-    const int64_t per_split = (int64_t)d.g * P->ctx_row_blocks;  // work-groups of one key split
-    // With the decode work-groups in a launch of their own: about one
-    // work-group per CU for eight-wave work-groups, two for four-wave ones;
-    // beside the side stream, one per CU (five eighths of that with eight
-    // waves of 32 rows: the decode work-groups take the rest).
-    const int target = P->fork ? (P->ctx_wide == 8 ? kCUs * 5 / 8 : kCUs)
-                               : (P->ctx_wide == 8 ? kCUs : 2 * kCUs);
+    const bool wide = !both || (wide_env == -1 ? one_launch || !P->fork || M >= 128 : wide_env == 1);
     const int wgs = env_int("BIFATTN_CTX_WGS", 0);
-    int64_t splits = wgs > 0      ? ceil_div(wgs, per_split)
-                     : one_launch ? fused_splits(P, per_split, M)
-                                  : ceil_div(target, per_split);
-    if (splits < 1) splits = 1;
-    const int64_t ck = round_up(ceil_div(d.m_c, splits), ck_step(key_step, d.m_c, splits));
+    ManySplit split;
+    if (one_launch && wgs == 0) {
+      split = many_row_split(P, M);
+    } else {
+      split.waves = M >= 256 ? 8 : 4;
+    }
+    P->ctx_wide = wide ? split.waves : 0;
+    const int block_rows = wide ? 32 * P->ctx_wide : kLargeRowsPerBlock;
+    P->ctx_row_blocks = (int)ceil_div(M, block_rows);
+    int key_step = wide ? 64 : kTileKeys;  // keys per stage of the kernel's loop
+    if (!one_launch || wgs > 0) {
+      // With the decode work-groups in a launch of their own: about one
+      // work-group per CU for eight-wave work-groups, two for four-wave ones;
+      // beside the side stream, one per CU (five eighths of that with eight
+      // waves of 32 rows: the decode work-groups take the rest).
+      const int target = P->fork ? (P->ctx_wide == 8 ? kCUs * 5 / 8 : kCUs)
+                                 : (P->ctx_wide == 8 ? kCUs : 2 * kCUs);
+      split.splits = ceil_div(wgs > 0 ? wgs : target, (int64_t)d.g * P->ctx_row_blocks);
+    }
+    if (coarse && !both) {
+      split.splits = ceil_div(2 * kCUs, d.g * ceil_div(M, kLargeRowsPerBlock));
+      key_step = kTileKeys;
+    }
+    const int64_t splits = std::max<int64_t>(1, split.splits);
+    int64_t ck = round_up(ceil_div(d.m_c, splits), ck_step(key_step, d.m_c, splits));
+    if (coarse && M <= 64) ck = long_keys;
     P->ctx_keys = (int)round_up(env_int("BIFATTN_CTX_KEYS", (int)ck), key_step);
   }
   P->S_c = (int)ceil_div(d.m_c, P->ctx_keys);

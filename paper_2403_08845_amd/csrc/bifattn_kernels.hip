@@ -1073,7 +1073,7 @@ ctx_large_kernel(PartialsParams P) {
 
 
 // ---------------------------------------------------------------------------
-// Context part, many query rows per group, d = 128 (any cache type), on
+// Context part, many query rows per group (any cache type), on
 // v_mfma_f32_32x32x16_bf16 (lane l, j = l % 32, h = l / 32):
 //   A (32 x 16): lane holds A[j][8h .. 8h+7]
 //   B (16 x 32): lane holds B[8h .. 8h+7][j]
@@ -1096,24 +1096,25 @@ ctx_large_kernel(PartialsParams P) {
 // at the instruction's base + 16 l, so the lane chooses which chunk of which
 // row to fetch); code caches load a stage into registers a stage ahead and
 // write it widened (stage_get / stage_put). Rows are padded in LDS, key
-// rows to 272 bytes and value rows to 288, which keeps both kinds of operand
-// reads free of bank conflicts (16 key rows of one read start 16 bytes
-// apart in the banks, the 4 value rows of one transposing read 32 bytes
-// apart) while every read address stays a per-lane base plus a constant;
+// rows by 16 bytes and value rows by 32, which keeps both kinds of operand
+// reads free of bank conflicts (the 16 key rows of one read start at
+// different 16-byte bank groups, the 4 value rows of one transposing read at
+// different 32-byte ones) while every read address stays a per-lane base
+// plus a constant;
 // the lanes that fill padding load from beyond the buffer's range, which
 // writes zeros without a memory access. One barrier per stage hands a
 // filled buffer to every wave and releases the oldest for refilling.
-namespace wide {
-constexpr int D = 128;
-constexpr int RB = D * 2;             // bytes per bf16 row
-constexpr int KSTEPS = D / 16;        // k-steps of the logits
-constexpr int DB = D / 32;            // 32-dim blocks of the output
-constexpr int KROW = RB + 16;         // padded key row in LDS
-constexpr int VROW = RB + 32;         // padded value row in LDS
-constexpr int KSLOTS = KROW / 16;     // 17 sixteen-byte slots per key row
-constexpr int VSLOTS = VROW / 16;     // 18 per value row
+template <int D> struct Wide {
+  static constexpr int RB = D * 2;          // bytes per bf16 row
+  static constexpr int KSTEPS = D / 16;     // k-steps of the logits
+  static constexpr int DB = D / 32;         // 32-dim blocks of the output
+  static constexpr int KROW = RB + 16;      // padded key row in LDS
+  static constexpr int VROW = RB + 32;      // padded value row in LDS
+  static constexpr int RSLOTS = RB / 16;    // sixteen-byte slots of data per row,
+  static constexpr int KSLOTS = KROW / 16;  // per padded key row
+  static constexpr int VSLOTS = VROW / 16;  // and per padded value row
+};
 constexpr uint32_t kBeyond = 0x80000000u;  // a byte offset past any cache chunk
-}  // namespace wide
 
 typedef __attribute__((address_space(3))) void lds_void;
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -1147,6 +1148,13 @@ __device__ __forceinline__ void lds_wait_tr(u32x2 (&w)[16]) {
                :
                : "memory");
 }
+__device__ __forceinline__ void lds_wait_tr(u32x2 (&w)[8]) {
+  asm volatile("s_waitcnt lgkmcnt(0)"
+               : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5]),
+                 "+v"(w[6]), "+v"(w[7])
+               :
+               : "memory");
+}
 // Key operand read (ds_read_b128) at LDS byte address addr + OFF, by inline
 // assembly like ds_tr16 (so that its wait can be placed by the caller, with
 // lds_wait_k, after the value products it overlaps).
@@ -1163,38 +1171,49 @@ __device__ __forceinline__ void lds_wait_k(u32x4 (&w)[8]) {
                :
                : "memory");
 }
-// The eight key operands (k-steps 0..7) of one 32-key block of key rows
-// padded to 272 bytes: read ks at 32 ks bytes from the lane's base.
+__device__ __forceinline__ void lds_wait_k(u32x4 (&w)[4]) {
+  asm volatile("s_waitcnt lgkmcnt(0)"
+               : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3])
+               :
+               : "memory");
+}
+// The key operands (k-steps 0 .. d/16 - 1) of one 32-key block of padded key
+// rows: read ks at 32 ks bytes from the lane's base.
 __device__ __forceinline__ void read_k_block(uint32_t a, u32x4 (&w)[8]) {
   w[0] = ds_b128<0>(a); w[1] = ds_b128<32>(a); w[2] = ds_b128<64>(a); w[3] = ds_b128<96>(a);
   w[4] = ds_b128<128>(a); w[5] = ds_b128<160>(a); w[6] = ds_b128<192>(a); w[7] = ds_b128<224>(a);
 }
-// The sixteen transposing reads of one 32-key block's V^T operands: read
-// (ss, t, r) of k-step ss, dims 32t .. 32t+31, half r, into w[8 ss + 2 t + r].
+__device__ __forceinline__ void read_k_block(uint32_t a, u32x4 (&w)[4]) {
+  w[0] = ds_b128<0>(a); w[1] = ds_b128<32>(a); w[2] = ds_b128<64>(a); w[3] = ds_b128<96>(a);
+}
+// The transposing reads of one 32-key block's V^T operands: read (ss, t, r)
+// of k-step ss, dims 32t .. 32t+31, half r, into w[2 DB ss + 2 t + r].
+#define BIFATTN_TR(n, ss, t, r) \
+  w[(n) * (ss) + 2 * (t) + (r)] = ds_tr16<(16 * (ss) + 8 * (r)) * VROW + 64 * (t)>(a)
 template <int VROW>
 __device__ __forceinline__ void read_vt_block(uint32_t a, u32x2 (&w)[16]) {
-#define BIFATTN_TR(ss, t, r) w[8 * (ss) + 2 * (t) + (r)] = ds_tr16<(16 * (ss) + 8 * (r)) * VROW + 64 * (t)>(a)
-  BIFATTN_TR(0, 0, 0); BIFATTN_TR(0, 0, 1); BIFATTN_TR(0, 1, 0); BIFATTN_TR(0, 1, 1);
-  BIFATTN_TR(0, 2, 0); BIFATTN_TR(0, 2, 1); BIFATTN_TR(0, 3, 0); BIFATTN_TR(0, 3, 1);
-  BIFATTN_TR(1, 0, 0); BIFATTN_TR(1, 0, 1); BIFATTN_TR(1, 1, 0); BIFATTN_TR(1, 1, 1);
-  BIFATTN_TR(1, 2, 0); BIFATTN_TR(1, 2, 1); BIFATTN_TR(1, 3, 0); BIFATTN_TR(1, 3, 1);
-#undef BIFATTN_TR
+  BIFATTN_TR(8, 0, 0, 0); BIFATTN_TR(8, 0, 0, 1); BIFATTN_TR(8, 0, 1, 0); BIFATTN_TR(8, 0, 1, 1);
+  BIFATTN_TR(8, 0, 2, 0); BIFATTN_TR(8, 0, 2, 1); BIFATTN_TR(8, 0, 3, 0); BIFATTN_TR(8, 0, 3, 1);
+  BIFATTN_TR(8, 1, 0, 0); BIFATTN_TR(8, 1, 0, 1); BIFATTN_TR(8, 1, 1, 0); BIFATTN_TR(8, 1, 1, 1);
+  BIFATTN_TR(8, 1, 2, 0); BIFATTN_TR(8, 1, 2, 1); BIFATTN_TR(8, 1, 3, 0); BIFATTN_TR(8, 1, 3, 1);
 }
+template <int VROW>
+__device__ __forceinline__ void read_vt_block(uint32_t a, u32x2 (&w)[8]) {
+  BIFATTN_TR(4, 0, 0, 0); BIFATTN_TR(4, 0, 0, 1); BIFATTN_TR(4, 0, 1, 0); BIFATTN_TR(4, 0, 1, 1);
+  BIFATTN_TR(4, 1, 0, 0); BIFATTN_TR(4, 1, 0, 1); BIFATTN_TR(4, 1, 1, 0); BIFATTN_TR(4, 1, 1, 1);
+}
+#undef BIFATTN_TR
 
 // Bytes of LDS of a context work-group's stage buffers.
-constexpr int wide_stage_bytes(int NB, int SK) { return NB * SK * (wide::KROW + wide::VROW); }
+template <int D> constexpr int wide_stage_bytes(int NB, int SK) {
+  return NB * SK * (Wide<D>::KROW + Wide<D>::VROW);
+}
 
-template <int NW, int NB, int SK, typename KV>
+template <int D, int NW, int NB, int SK, typename KV>
 __device__ __forceinline__ void ctx_wide_block(const PartialsParams& P, unsigned char* lds) {
-  using wide::D;
-  using wide::RB;
-  using wide::KSTEPS;
-  using wide::DB;
-  using wide::KROW;
-  using wide::VROW;
-  using wide::KSLOTS;
-  using wide::VSLOTS;
-  using wide::kBeyond;
+  constexpr int RB = Wide<D>::RB, KSTEPS = Wide<D>::KSTEPS, DB = Wide<D>::DB;
+  constexpr int KROW = Wide<D>::KROW, VROW = Wide<D>::VROW;
+  constexpr int KSLOTS = Wide<D>::KSLOTS, VSLOTS = Wide<D>::VSLOTS;
   constexpr int KAREA = SK * KROW;
   constexpr int VAREA = SK * VROW;
   constexpr int STAGE = KAREA + VAREA;
@@ -1233,9 +1252,10 @@ __device__ __forceinline__ void ctx_wide_block(const PartialsParams& P, unsigned
     const int vs = slot - KAREA / 16;
     const int row = is_v ? vs / VSLOTS : slot / KSLOTS;
     const int c = is_v ? vs % VSLOTS : slot % KSLOTS;
-    loff[u] = c < 16 ? (uint32_t)(row * RB + c * 16) : kBeyond;
+    loff[u] = c < Wide<D>::RSLOTS ? (uint32_t)(row * RB + c * 16) : kBeyond;
   }
   auto fetch = [&](int key0, int buf) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the host pass does not know the 16-byte load
     const int rows = nkeys - key0;  // rows from the stage's first key to the chunk's end
     const __amdgpu_buffer_rsrc_t rk = rows_rsrc(kchunk + (size_t)key0 * CRB, rows, CRB);
     const __amdgpu_buffer_rsrc_t rv = rows_rsrc(vchunk + (size_t)key0 * CRB, rows, CRB);
@@ -1244,12 +1264,11 @@ __device__ __forceinline__ void ctx_wide_block(const PartialsParams& P, unsigned
       if (u < nload) {
         const int i = wave + NW * u;  // wave-uniform
         lds_void* dst = (lds_void*)(lds + buf * STAGE + i * 1024);
-#if defined(__HIP_DEVICE_COMPILE__)  // the host pass does not know the 16-byte form
         __builtin_amdgcn_raw_ptr_buffer_load_lds(i < KAREA / 1024 ? rk : rv, dst, 16,
                                                  boff(loff[u]), 0, 0, 0);
-#endif
       }
     }
+#endif
   };
   // This wave's loads of stage st are complete once at most the loads of
   // the one stage issued after it are in flight (or none, at the end).
@@ -1263,7 +1282,7 @@ __device__ __forceinline__ void ctx_wide_block(const PartialsParams& P, unsigned
   };
 
   // Q^T operands: k-step ks holds dims 16ks + 8h .. +7 of query row j.
-  // Rows past M load row M - 1 and are zeroed afterwards, so that the eight
+  // Rows past M load row M - 1 and are zeroed afterwards, so that the
   // loads issue back to back (a load under a per-lane condition waits for
   // its data before the next one issues).
   u32x4 qop[KSTEPS];
@@ -1384,7 +1403,7 @@ __device__ __forceinline__ void ctx_wide_block(const PartialsParams& P, unsigned
       // this block's V^T operands, read while the weights are formed (after
       // the key operand reads, whose waits would otherwise cover them too)
       __builtin_amdgcn_sched_barrier(0);
-      u32x2 vw[16];
+      u32x2 vw[4 * DB];
       read_vt_block<VROW>(vaddr + 32 * b * VROW, vw);
       float x[16];
 #pragma unroll
@@ -1443,7 +1462,7 @@ __device__ __forceinline__ void ctx_wide_block(const PartialsParams& P, unsigned
       for (int ss = 0; ss < 2; ++ss)
 #pragma unroll
         for (int t = 0; t < DB; ++t) {
-          const u32x2 lo = vw[8 * ss + 2 * t], hi = vw[8 * ss + 2 * t + 1];
+          const u32x2 lo = vw[2 * DB * ss + 2 * t], hi = vw[2 * DB * ss + 2 * t + 1];
           acc[t] = mfma32(u32x4{lo[0], lo[1], hi[0], hi[1]}, pb[ss], acc[t]);
         }
       if (b + 1 < SK / 32) lds_wait_k(kw);
@@ -1468,16 +1487,15 @@ __device__ __forceinline__ void ctx_wide_block(const PartialsParams& P, unsigned
 
 // Grid: n_ctx_blocks context work-groups, then one work-group for every
 // NW / 4 of the n_dec_blocks decode work-groups, whose waves are independent.
-template <int NW, int NB, int SK, typename KV, int NTD>
+template <int D, int NW, int NB, int SK, typename KV, int NTD>
 __device__ __forceinline__ void ctx_wide_body(const PartialsParams& P) {
-  constexpr int D = wide::D;
   constexpr int QB = NTD * (D / 32) * 64 * 16;  // bytes of a decode wave's Q^T operands
   constexpr int KB = kTileKeys * D * 2;         // and of its K tile
-  constexpr int LDS = cmax(wide_stage_bytes(NB, SK), NW * (QB + KB));
+  constexpr int LDS = cmax(wide_stage_bytes<D>(NB, SK), NW * (QB + KB));
   __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS];
   const int bid = blockIdx.x;
   if (bid < P.n_ctx_blocks) {
-    ctx_wide_block<NW, NB, SK, KV>(P, lds);
+    ctx_wide_block<D, NW, NB, SK, KV>(P, lds);
     return;
   }
   const int lane = threadIdx.x & 63, wave = wave_id();
@@ -1489,10 +1507,10 @@ __device__ __forceinline__ void ctx_wide_body(const PartialsParams& P) {
   }
 }
 
-template <int NW, int NB, int SK, typename KV, int NTD>
+template <int D, int NW, int NB, int SK, typename KV, int NTD>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void
 ctx_wide_kernel(PartialsParams P) {
-  ctx_wide_body<NW, NB, SK, KV, NTD>(P);
+  ctx_wide_body<D, NW, NB, SK, KV, NTD>(P);
 }
 
 // Grid: n_ctx_small_blocks work-groups of the few-row context path, then
@@ -1659,7 +1677,11 @@ hipError_t launch_partials_ctx(const PartialsParams& P, int dec_tiles, hipStream
                                const LaunchEvents& ev) {
   const int grid = P.n_ctx_small_blocks + P.n_dec_blocks;
   if (grid == 0) return hipSuccess;
-  switch (dec_tiles) {
+  // Four context tiles go with four decode tiles only (units of more than 32 rows).
+  if constexpr (CTX == kCtxSmall4) {
+    if (dec_tiles != 4) return hipErrorInvalidValue;
+    return launch(partials_kernel<D, KV, CTX, 4>, grid, kThreads, stream, ev, P);
+  } else switch (dec_tiles) {
     case 1:
       if constexpr (fits_two_waves<D, CTX, 1>())
         return launch(partials_kernel_2w<D, KV, CTX, 1>, grid, kThreads, stream, ev, P);
@@ -1723,36 +1745,46 @@ hipError_t launch_standard_d(const PartialsParams& P, int kv, int tiles, hipStre
   }
 }
 
-template <typename KV, int NTD>
+template <int D, typename KV, int NTD>
 hipError_t launch_ctx_wide_kv(const PartialsParams& P, hipStream_t stream,
                               const LaunchEvents& ev) {
   constexpr bool kDirect = KV::BITS == 16;
-  // eight waves: 128-key stages, two in LDS (fewer barriers than 64-key
-  // stages, measured 3-5% faster); chunks of a multiple of 64 keys (three
-  // 64-key stages in LDS for bf16, two for code caches, which stage a
-  // third in registers)
   const int per = P.ctx_wide / kWaves;  // decode work-groups in one of the launch's
   if (per < 1) return hipErrorInvalidValue;
   const int grid = P.n_ctx_blocks + (P.n_dec_blocks + per - 1) / per;
+  // eight waves: 128-key stages, two in LDS (fewer barriers than 64-key
+  // stages, measured 3-5% faster); d = 128 and chunks of a multiple of 64 keys: three
+  // 64-key stages in LDS for bf16, two for code caches, which stage a
+  // third in registers
   if (P.ctx_wide == 8) {
-    if (P.ctx_keys % 128 == 0)
-      return launch(ctx_wide_kernel<8, 2, 128, KV, NTD>, grid, 512, stream, ev, P);
-    return launch(ctx_wide_kernel<8, kDirect ? 3 : 2, 64, KV, NTD>, grid, 512, stream, ev, P);
+    if constexpr (D == 128)
+      if (P.ctx_keys % 128 != 0)
+        return launch(ctx_wide_kernel<D, 8, kDirect ? 3 : 2, 64, KV, NTD>, grid, 512, stream, ev, P);
+    return launch(ctx_wide_kernel<D, 8, 2, 128, KV, NTD>, grid, 512, stream, ev, P);
   }
-  if (P.ctx_wide == 4) return launch(ctx_wide_kernel<4, 2, 64, KV, NTD>, grid, 256, stream, ev, P);
+  if (P.ctx_wide == 4)
+    return launch(ctx_wide_kernel<D, 4, 2, 64, KV, NTD>, grid, 256, stream, ev, P);
   return hipErrorInvalidValue;
 }
 
-template <int NTD>
-hipError_t launch_ctx_wide(const PartialsParams& P, int kv, hipStream_t stream,
-                           const LaunchEvents& ev) {
+template <int D, int NTD>
+hipError_t launch_ctx_wide_n(const PartialsParams& P, int kv, hipStream_t stream,
+                             const LaunchEvents& ev) {
   switch (kv) {
-    case kKvBf16: return launch_ctx_wide_kv<KvBf16, NTD>(P, stream, ev);
-    case kKvFp8: return launch_ctx_wide_kv<KvFp8, NTD>(P, stream, ev);
-    case kKvInt8: return launch_ctx_wide_kv<KvInt8, NTD>(P, stream, ev);
-    case kKvInt4: return launch_ctx_wide_kv<KvInt4, NTD>(P, stream, ev);
+    case kKvBf16: return launch_ctx_wide_kv<D, KvBf16, NTD>(P, stream, ev);
+    case kKvFp8: return launch_ctx_wide_kv<D, KvFp8, NTD>(P, stream, ev);
+    case kKvInt8: return launch_ctx_wide_kv<D, KvInt8, NTD>(P, stream, ev);
+    case kKvInt4: return launch_ctx_wide_kv<D, KvInt4, NTD>(P, stream, ev);
     default: return hipErrorInvalidValue;
   }
+}
+
+template <int D>
+hipError_t launch_ctx_wide(const PartialsParams& P, int kv, int dec_tiles, hipStream_t stream,
+                           const LaunchEvents& ev) {
+  if (P.n_dec_blocks > 0 && dec_tiles > 2) return hipErrorInvalidValue;
+  return P.n_dec_blocks > 0 && dec_tiles == 2 ? launch_ctx_wide_n<D, 2>(P, kv, stream, ev)
+                                              : launch_ctx_wide_n<D, 1>(P, kv, stream, ev);
 }
 
 template <int D>
@@ -1843,15 +1875,12 @@ hipError_t launch_ctx_large(const PartialsParams& P, int d, int kv, int dec_tile
                             hipStream_t stream, const LaunchEvents& ev) {
   if (P.n_ctx_blocks == 0) return hipSuccess;
   if (P.ctx_wide) {
-    if (d != 128) return hipErrorInvalidValue;
-    if (P.n_dec_blocks > 0 && dec_tiles > 2) return hipErrorInvalidValue;
-    return P.n_dec_blocks > 0 && dec_tiles == 2 ? launch_ctx_wide<2>(P, kv, stream, ev)
-                                                : launch_ctx_wide<1>(P, kv, stream, ev);
+    if (d == 128) return launch_ctx_wide<128>(P, kv, dec_tiles, stream, ev);
+    if (d == 64) return launch_ctx_wide<64>(P, kv, dec_tiles, stream, ev);
+    return hipErrorInvalidValue;
   }
-  if (P.n_dec_blocks > 0) return hipErrorInvalidValue;
-  if (d == 128) return launch_ctx_large_d<128>(P, kv, stream, ev);
-  if (d == 64) return launch_ctx_large_d<64>(P, kv, stream, ev);
-  return hipErrorInvalidValue;
+  if (P.n_dec_blocks > 0 || d != 128) return hipErrorInvalidValue;
+  return launch_ctx_large_d<128>(P, kv, stream, ev);
 }
 hipError_t launch_standard(const PartialsParams& P, int d, int kv, int tiles,
                            hipStream_t stream, const LaunchEvents& ev) {

@@ -67,8 +67,9 @@ def test_noalloc_takes_the_problems_whose_longest_chunks_fit():
     (2, 32, 8, 128, 3001, 200, 1, "bf16"),   # 256-key chunks, the last one short
     (3, 16, 4, 64, 257, 40, 2, "bf16"),      # one key in the second chunk
     (1, 4, 1, 128, 1, 1, 1, "bf16"),         # the smallest
-    (20, 8, 4, 128, 5000, 300, 1, "int8"),   # 256-key chunks, one decode chunk of 384
-    (16, 32, 8, 128, 6000, 1000, 1, "bf16"),  # M = 64, two decode chunks
+    (16, 8, 4, 128, 5000, 300, 1, "int8"),   # 256-key chunks, one decode chunk of 384
+    (8, 32, 8, 128, 6000, 1000, 1, "bf16"),  # 32 rows per group, two decode chunks
+    (1, 64, 1, 128, 3000, 100, 1, "bf16"),   # 64 rows of one unit
     (4, 40, 40, 128, 1300, 600, 1, "int4"),
     (9, 32, 32, 64, 2100, 30, 1, "fp8_e4m3"),
 ], ids=lambda c: "b%d_h%d_g%d_d%d_mc%d_md%d_n%d_%s" % c)
@@ -106,6 +107,15 @@ def test_short_chunks_match_the_oracle(case):
     (13, 20, 4, 128, 640, 70, 4, "int8"),      # tokens
     (65, 8, 8, 128, 3000, 5, 1, "int4"),       # one decode tile
     (70, 4, 1, 128, 130, 1, 1, "bf16"),        # a second key chunk of two keys
+    (33, 4, 4, 128, 500, 60, 1, "bf16"),       # 33 rows per group: one row in the second wave
+    (16, 4, 1, 128, 64, 40, 1, "int8"),        # 64 rows, one stage
+    (33, 2, 2, 64, 700, 33, 1, "bf16"),        # d = 64: four waves,
+    (50, 24, 2, 64, 1111, 130, 1, "bf16"),     # three row blocks or more, an idle wave
+    (128, 32, 1, 64, 9000, 64, 1, "bf16"),     # eight waves, two query tiles per unit
+    (64, 32, 2, 64, 9001, 40, 1, "fp8_e4m3"),
+    (64, 32, 2, 64, 9001, 40, 1, "int8"),
+    (64, 32, 2, 64, 9001, 40, 2, "int4"),
+    (20, 8, 4, 64, 1, 3, 1, "int4"),           # one context key
 ], ids=lambda c: "b%d_h%d_g%d_d%d_mc%d_md%d_n%d_%s" % c)
 def test_many_rows_in_one_launch_equal_two(case, monkeypatch):
     """The decode work-groups in the 32x32 context kernel's launch: the same
