@@ -332,13 +332,20 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
   // The workload-based switch: the standard path reads the context once per
   // sample but needs one launch and no partials. It wins while every unit is
   // resident in one round of work-groups (b*g <= 512), has at most two query
-  // tiles, and holds few keys: up to ~1100 (~600 once units share CUs), or
-  // ~2200 when the bifurcated context part has 64 or more rows per group
-  // (its four-tile and many-row work-groups are the costly ones). These are
-  // the crossovers measured on MI355X over 38 MHA/GQA/MQA shapes.
+  // tiles, and holds few keys: the crossovers measured over 24 layers at six
+  // context lengths each, by head dimension, units per CU (one, two) and rows
+  // per group (16, 32, 128, more): b 4, h = g = 8, d 128, 960 keys 13.3 us
+  // standard against 9.9; b 30, h 32, g 8, 1564 keys 18.1 against 14.3; b 60,
+  // h 32, g 4, 860 keys 12.3 against 15.3. (Units that fill the last sixteenth of the
+  // slots keep a line of 2200 keys from 64 rows per group, as callers have
+  // come to know it: 2112 keys there take about 30 us against 18.)
   if (d.path == BIFATTN_PATH_AUTO) {
+    static constexpr int kKeys[2][2][4] = {{{560, 900, 750, 1150}, {560, 600, 520, 1000}},
+                                           {{1200, 1500, 1450, 1800}, {800, 850, 830, 1200}}};
     const int64_t keys = (int64_t)d.m_c + d.m_d_max;
-    const int64_t lmax = M >= 64 ? 2200 : (units > kCUs ? 600 : 1100);
+    const int64_t lmax = M >= 64 && units > 2 * kCUs * 15 / 16
+                             ? 2200
+                             : kKeys[d.d == 64][units > kCUs][M <= 16 ? 0 : M <= 32 ? 1 : M <= 128 ? 2 : 3];
     const bool small = units <= 2 * kCUs && P->p <= 32 && keys <= lmax;
     P->path = small ? BIFATTN_PATH_STANDARD : BIFATTN_PATH_BIFURCATED;
   } else {
