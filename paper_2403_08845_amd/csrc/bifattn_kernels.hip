@@ -243,6 +243,27 @@ struct KvInt4 : KvBits<4> {
   }
 };
 
+// int4 codes in the streaming waves: their widening is what bounds them (320 of
+// ~370 vector instructions per 32-key tile when every code was sign-extended,
+// converted and packed: 2.5 instructions a code). Instead a code's nibble goes
+// straight into the mantissa of a bf16 16.0 (bits 3-6, its sign bit flipped):
+// the value is code + 24, exactly, at one shift and one v_bitop3 for two codes.
+// The constant leaves the logits through their first accumulator (-24 sum(q))
+// and the weighted values through the sum of the rounded weights. Nibble t of
+// a word pairs with nibble t + 4, so Q^T operands take the same order.
+constexpr float kInt4Offset = 24.f;
+__device__ __forceinline__ uint32_t int4_pair(uint32_t w, int t) {  // nibbles t and t + 4
+  const uint32_t x = t == 0 ? w << 3 : w >> (4 * t - 3);
+  return (x & 0x00780078u) ^ 0x41C041C0u;
+}
+// The order of int4_pair within 8 bf16 elements: (0,4) (1,5) (2,6) (3,7).
+__device__ __forceinline__ u32x4 int4_order(const u32x4& q) {
+  return u32x4{__builtin_amdgcn_perm(q[2], q[0], 0x05040100u),
+               __builtin_amdgcn_perm(q[2], q[0], 0x07060302u),
+               __builtin_amdgcn_perm(q[3], q[1], 0x05040100u),
+               __builtin_amdgcn_perm(q[3], q[1], 0x07060302u)};
+}
+
 // 8 cache elements -> 8 bf16 (one MFMA operand): 16 raw bytes (bf16) as
 // they are, or 8 codes widened.
 template <typename KV> struct Widen8;
@@ -288,13 +309,19 @@ __device__ __forceinline__ int qk_key(int a, int r) { return 16 * a + 4 * (r & 3
 // lacc holds the row's sum of the bf16-rounded weights (the weights the
 // values are multiplied by) in all four of its elements, instead of the
 // lane's share of the fp32 weights in l.
-template <int D, int NT, bool MS = false> struct RowState {
+// With OFF (int4 caches of the streaming waves, see Int4Offset) the operands
+// hold each code's value plus an offset: bias starts every logit at minus the
+// offset's share, and lacc's sums of the rounded weights take it out of acc
+// at the end.
+template <int D, int NT, bool MS = false, bool OFF = false> struct RowState {
   static constexpr int DV = D / 16;
+  static constexpr bool kSums = MS || OFF;  // sums of the rounded weights by the matrix cores
   float mref[NT];       // reference maximum (log2 units), uniform over the row's 4 lanes
   float nbase[MS ? NT : 1];  // with MS: -mref, or 0 while mref = -inf (the exponent's offset)
   float thr[NT];        // raw-logit threshold: a logit above it calls for a higher mref
   float l[NT];          // this lane's share of the row sum (without MS)
-  f32x4 lacc[MS ? NT : 1];  // row sums (with MS)
+  f32x4 lacc[kSums ? NT : 1];  // sums of the rounded weights (with MS or OFF)
+  f32x4 bias[OFF ? NT : 1];    // first accumulator of the logits (with OFF)
   f32x4 acc[NT][DV];    // O^T accumulators
   __device__ __forceinline__ void init() {
 #pragma unroll
@@ -303,7 +330,7 @@ template <int D, int NT, bool MS = false> struct RowState {
       if constexpr (MS) nbase[nt] = 0.f;
       thr[nt] = kNegInf;
       l[nt] = 0.f;
-      if constexpr (MS) lacc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (kSums) lacc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int t = 0; t < DV; ++t) acc[nt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
@@ -321,8 +348,8 @@ template <int D, int NT, bool MS = false> struct RowState {
 // (ntok = 1 masks keys >= rem). Keys below `vfloor` (counted from the tile's
 // first key, like rem) are seen by every row whatever its causal limit: the
 // context rows that precede the decode rows in a replicated cache.
-template <int D, int NT, bool MS, typename KOp, typename VOp, typename QOp>
-__device__ __forceinline__ void tile_update(RowState<D, NT, MS>& st, KOp&& k_at, VOp&& vop_at,
+template <int D, int NT, bool MS, bool OFF, typename KOp, typename VOp, typename QOp>
+__device__ __forceinline__ void tile_update(RowState<D, NT, MS, OFF>& st, KOp&& k_at, VOp&& vop_at,
                                             QOp&& q_at, int rem, int ntok, int vfloor,
                                             float scale_log2, int lane) {
   constexpr int KS = D / 32;
@@ -330,7 +357,12 @@ __device__ __forceinline__ void tile_update(RowState<D, NT, MS>& st, KOp&& k_at,
   const int G = lane >> 4;
   f32x4 sacc[NT][2];
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) sacc[nt][0] = sacc[nt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int nt = 0; nt < NT; ++nt) {
+    if constexpr (OFF)
+      sacc[nt][0] = sacc[nt][1] = st.bias[nt];
+    else
+      sacc[nt][0] = sacc[nt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
   if constexpr (MS) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
   for (int s = 0; s < KS; ++s) {
@@ -383,10 +415,8 @@ __device__ __forceinline__ void tile_update(RowState<D, NT, MS>& st, KOp&& k_at,
       // Rows that do not raise keep alpha = 1 (and never form -inf - -inf).
       const bool raise = tmax > st.mref[nt] + kRescaleSlack;
       const float alpha = raise ? exp2_fast(st.mref[nt] - tmax) : 1.f;  // 0 when mref = -inf
-      if constexpr (MS)
-        st.lacc[nt] *= alpha;
-      else
-        st.l[nt] *= alpha;
+      if constexpr (MS || OFF) st.lacc[nt] *= alpha;
+      if constexpr (!MS) st.l[nt] *= alpha;
 #pragma unroll
       for (int t = 0; t < DV; ++t) st.acc[nt][t] *= alpha;
       st.mref[nt] = raise ? tmax : st.mref[nt];
@@ -413,7 +443,7 @@ __device__ __forceinline__ void tile_update(RowState<D, NT, MS>& st, KOp&& k_at,
     u32x4 pb;
 #pragma unroll
     for (int w = 0; w < 4; ++w) pb[w] = pack_bf16(pr[2 * w], pr[2 * w + 1]);
-    if constexpr (MS) {
+    if constexpr (MS || OFF) {
       constexpr uint32_t kOnes = 0x3F803F80u;  // two bf16 1.0
       st.lacc[nt] = mfma_bf16(u32x4{kOnes, kOnes, kOnes, kOnes}, pb, st.lacc[nt]);
     }
@@ -543,7 +573,8 @@ template <int D, typename KV> struct TileRegs {
         // 32 codes: bf16 chunks 4c .. 4c + 3 of the row.
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-          *(lds_u32x4*)(kl + kslot(row, 4 * c + k)) = Widen8<KV>::run(w[k]);
+          *(lds_u32x4*)(kl + kslot(row, 4 * c + k)) =
+              u32x4{int4_pair(w[k], 0), int4_pair(w[k], 1), int4_pair(w[k], 2), int4_pair(w[k], 3)};
       }
     }
     __builtin_amdgcn_wave_barrier();
@@ -565,7 +596,13 @@ template <int D, typename KV> struct TileRegs {
   __device__ __forceinline__ u32x4 vop(int t) const {
     u32x4 v;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) v[w] = value_pair<KV>(vrow[2 * w], vrow[2 * w + 1], t);
+    for (int w = 0; w < 4; ++w) {
+      if constexpr (KV::BITS == 4)  // half a row's nibbles beside half of the other's
+        v[w] = int4_pair(__builtin_amdgcn_perm(vrow[2 * w + 1], vrow[2 * w],
+                                               t < 4 ? 0x05040100u : 0x07060302u), t % 4);
+      else
+        v[w] = value_pair<KV>(vrow[2 * w], vrow[2 * w + 1], t);
+    }
     return v;
   }
 };
@@ -579,22 +616,25 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const uint8_t* base,
 }
 
 // Row totals of the per-lane sums (the four lanes of a row share the row).
-template <int D, int NT, bool MS>
-__device__ __forceinline__ void finish_sums(RowState<D, NT, MS>& st) {
+template <int D, int NT, bool MS, bool OFF>
+__device__ __forceinline__ void finish_sums(RowState<D, NT, MS, OFF>& st) {
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     if constexpr (MS)
       st.l[nt] = st.lacc[nt][0];
     else
       st.l[nt] = xor32_sum(xor16_sum(st.l[nt]));
+    if constexpr (OFF)
+#pragma unroll
+      for (int t = 0; t < D / 16; ++t) st.acc[nt][t] -= kInt4Offset * st.lacc[nt];
   }
 }
 
 // Write the wave's partials of rows row0 + nt*16 + n < nrows: lane (n, G)
 // stores dims [4*DV*G, 4*DV*G + 4*DV) of its row (contiguous), lane G = 0
 // the row's (m, l).
-template <int D, int NT>
-__device__ __forceinline__ void store_partials(RowState<D, NT>& st, int nrows, float* acc_out,
+template <int D, int NT, bool OFF>
+__device__ __forceinline__ void store_partials(RowState<D, NT, false, OFF>& st, int nrows, float* acc_out,
                                                float2* ml_out, int lane) {
   constexpr int DV = D / 16;
   const int n = lane & 15, G = lane >> 4;
@@ -616,6 +656,28 @@ __device__ __forceinline__ void store_partials(RowState<D, NT>& st, int nrows, f
   }
 }
 
+// Running state of a streaming wave over caches of type KV.
+template <int D, int NT, typename KV> using StreamState = RowState<D, NT, false, KV::BITS == 4>;
+
+// The logits' first accumulator of a streaming wave over int4 codes, after
+// its Q^T operands are staged: minus the offset times the sum of the row's q.
+template <int D, int NT, typename KV>
+__device__ __forceinline__ void start_stream(StreamState<D, NT, KV>& st, const u32x4* qw, int lane) {
+  if constexpr (KV::BITS == 4) {
+    constexpr uint32_t kMinus = 0xC1C0C1C0u;  // two bf16 -kInt4Offset
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      f32x4 b = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < D / 32; ++s) {
+        const u32x4 q = *(volatile const lds_u32x4*)(qw + (nt * (D / 32) + s) * 64 + lane);
+        b = mfma_bf16(u32x4{kMinus, kMinus, kMinus, kMinus}, q, b);
+      }
+      st.bias[nt] = b;
+    }
+  }
+}
+
 // One wave streams the 32-key tiles starting at keys k0, k0 + stride,
 // k0 + 2*stride, ... below k1 of one cache segment (buffer resources rk/rv
 // over its rows) through tile_update, double-buffered: the loads of the
@@ -628,7 +690,7 @@ __device__ __forceinline__ void store_partials(RowState<D, NT>& st, int nrows, f
 // sequence the tokens' causal limits count from (ntok tokens per unit; k1
 // when ntok = 1); keys below vis0 are seen by every token.
 template <int D, int NT, typename KV, int AUX = kAuxStream>
-__device__ __forceinline__ void stream_keys(RowState<D, NT>& st, const u32x4* qw, u32x4* kl,
+__device__ __forceinline__ void stream_keys(StreamState<D, NT, KV>& st, const u32x4* qw, u32x4* kl,
                                             __amdgpu_buffer_rsrc_t rk, __amdgpu_buffer_rsrc_t rv,
                                             TileRegs<D, KV>& A, int k0, int k1, int kend, int stride,
                                             int ntok, int vis0, float scale_log2, int lane) {
@@ -650,7 +712,7 @@ __device__ __forceinline__ void stream_keys(RowState<D, NT>& st, const u32x4* qw
     const int nv0 = min(kTileKeys, k1 - key);
     if (nv0 < kTileKeys) A.mask_v(nv0, lane);
     A.stage_k(kl, lane);
-    tile_update<D, NT>(st, k_at, [&](int t) { return A.vop(t); }, q_at, kend - key, ntok,
+    tile_update(st, k_at, [&](int t) { return A.vop(t); }, q_at, kend - key, ntok,
                        vis0 - key, scale_log2, lane);
     if (key1 >= k1) break;
     const int key2 = key1 + stride;
@@ -658,7 +720,7 @@ __device__ __forceinline__ void stream_keys(RowState<D, NT>& st, const u32x4* qw
     const int nv1 = min(kTileKeys, k1 - key1);
     if (nv1 < kTileKeys) B.mask_v(nv1, lane);
     B.stage_k(kl, lane);
-    tile_update<D, NT>(st, k_at, [&](int t) { return B.vop(t); }, q_at, kend - key1, ntok,
+    tile_update(st, k_at, [&](int t) { return B.vop(t); }, q_at, kend - key1, ntok,
                        vis0 - key1, scale_log2, lane);
     if (key2 >= k1) break;
   }
@@ -667,7 +729,7 @@ __device__ __forceinline__ void stream_keys(RowState<D, NT>& st, const u32x4* qw
 // Stage this wave's Q^T operands of NT query tiles in its LDS slice qw.
 // row_ptr(r) gives the bf16 row of tile row r (r = nt*16 + n) or nullptr
 // for padding rows.
-template <int D, int NT, typename RowPtr>
+template <int D, int NT, typename KV, typename RowPtr>
 __device__ __forceinline__ void stage_q(u32x4* qw, RowPtr row_ptr, uint32_t sign, int lane) {
   constexpr int KS = D / 32;
   u32x4 qop[NT][KS];
@@ -676,7 +738,8 @@ __device__ __forceinline__ void stage_q(u32x4* qw, RowPtr row_ptr, uint32_t sign
   for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
     for (int s = 0; s < KS; ++s)
-      *(volatile lds_u32x4*)(qw + (nt * KS + s) * 64 + lane) = qop[nt][s];
+      *(volatile lds_u32x4*)(qw + (nt * KS + s) * 64 + lane) =
+          KV::BITS == 4 ? int4_order(qop[nt][s]) : qop[nt][s];
 }
 
 // Softmax scale of group gam's units in log2 units, the key scale folded in
@@ -723,23 +786,24 @@ __device__ void decode_block(const PartialsParams& P, int blk, int wave, int lan
   const __amdgpu_buffer_rsrc_t rv1 = rows_rsrc(P.Vd + cache, k1, RB);
   const uint16_t* qbase = P.q + ((size_t)i * P.h + (size_t)gam * P.p) * D;
   const int p = P.p;
-  stage_q<D, NT>(qw, [&](int r) -> const uint16_t* { return r < p ? qbase + (size_t)r * D : nullptr; },
+  stage_q<D, NT, KV>(qw, [&](int r) -> const uint16_t* { return r < p ? qbase + (size_t)r * D : nullptr; },
                  P.q_sign, lane);
-  RowState<D, NT> st;
+  StreamState<D, NT, KV> st;
   st.init();
+  start_stream<D, NT, KV>(st, qw, lane);
   // Keys [k0, k1) of this chunk; the causal limits of the tokens count from
   // the end of the sequence (total), which may lie in a later chunk.
   stream_keys<D, NT, KV>(st, qw, kl, rk1, rv1, A, k0, k1, total, kWaves * kTileKeys, P.ntok,
                          P.len_offset, unit_scale_log2(P, gam), lane);
   const size_t prow = ((size_t)blk * kWaves + wave) * P.p;
-  store_partials<D, NT>(st, p, P.dec_acc + prow * D, P.dec_ml + prow, lane);
+  store_partials(st, p, P.dec_acc + prow * D, P.dec_ml + prow, lane);
 }
 
 // Merge the four waves' states of the same NT*16 rows through LDS, in wave
 // order (so the result is deterministic): afterwards row r's merged partial
 // is acc_s[r*LD ..], m_s[r], l_s[r] (LD = d + 4), visible to every thread.
-template <int D, int NT>
-__device__ __forceinline__ void merge_waves(RowState<D, NT>& st, float* lds, int wave, int lane) {
+template <int D, int NT, bool OFF>
+__device__ __forceinline__ void merge_waves(RowState<D, NT, false, OFF>& st, float* lds, int wave, int lane) {
   constexpr int DV = D / 16;
   constexpr int LD = D + 4;  // padded LDS row
   constexpr int ROWS = NT * kRowsPerTile;
@@ -782,13 +846,13 @@ __device__ __forceinline__ void merge_waves(RowState<D, NT>& st, float* lds, int
 
 // Merge the waves' states and write rows < nrows of the merged partial to
 // acc_out / ml_out.
-template <int D, int NT>
-__device__ __forceinline__ void merge_waves_and_store(RowState<D, NT>& st, float* lds, int nrows,
+template <int D, int NT, bool OFF>
+__device__ __forceinline__ void merge_waves_and_store(RowState<D, NT, false, OFF>& st, float* lds, int nrows,
                                                       float* acc_out, float2* ml_out, int wave,
                                                       int lane) {
   constexpr int LD = D + 4;
   constexpr int ROWS = NT * kRowsPerTile;
-  merge_waves<D, NT>(st, lds, wave, lane);
+  merge_waves(st, lds, wave, lane);
   const float* acc_s = lds;
   const float* m_s = lds + ROWS * LD;
   const float* l_s = m_s + ROWS;
@@ -824,18 +888,19 @@ __device__ void ctx_small_block(const PartialsParams& P, int blk, int wave, int 
   A.load(rk, rv, k0, lane);  // first tile in flight while Q is staged
   const int M = P.M, p = P.p, h = P.h;
   const uint16_t* q = P.q;
-  stage_q<D, NT>(qw, [&](int r) -> const uint16_t* {
+  stage_q<D, NT, KV>(qw, [&](int r) -> const uint16_t* {
     if (r >= M) return nullptr;
     const int i = r / p, jp = r - i * p;
     return q + ((size_t)i * h + (size_t)gam * p + jp) * D;
   }, P.q_sign, lane);
-  RowState<D, NT> st;
+  StreamState<D, NT, KV> st;
   st.init();
+  start_stream<D, NT, KV>(st, qw, lane);
   stream_keys<D, NT, KV>(st, qw, kl, rk, rv, A, k0, P.m_c, P.m_c, P.S_c * kWaves * kTileKeys, 1,
                          0, unit_scale_log2(P, gam), lane);
   const size_t prow = (size_t)blk * P.M;
   __syncthreads();  // the merge buffer overlays the waves' K tiles
-  merge_waves_and_store<D, NT>(st, merge_lds, M, P.ctx_acc + prow * D, P.ctx_ml + prow, wave, lane);
+  merge_waves_and_store(st, merge_lds, M, P.ctx_acc + prow * D, P.ctx_ml + prow, wave, lane);
 }
 
 // Standard attention, the other side of the workload-based switch (FAQ on
@@ -866,11 +931,12 @@ __device__ void standard_block(const PartialsParams& P, int blk, int wave, int l
   A.template load<0>(rkc, rvc, k0, lane);  // first context tile in flight during the set-up
   const int p = P.p;
   const uint16_t* qbase = P.q + ((size_t)i * P.h + (size_t)gam * p) * D;
-  stage_q<D, NT>(qw, [&](int r) -> const uint16_t* { return r < p ? qbase + (size_t)r * D : nullptr; },
+  stage_q<D, NT, KV>(qw, [&](int r) -> const uint16_t* { return r < p ? qbase + (size_t)r * D : nullptr; },
                  P.q_sign, lane);
   const float sl2 = unit_scale_log2(P, gam);
-  RowState<D, NT> st;
+  StreamState<D, NT, KV> st;
   st.init();
+  start_stream<D, NT, KV>(st, qw, lane);
   // Context rows: visible to every token (a causal limit only applies among
   // the decode rows).
   stream_keys<D, NT, KV, 0>(st, qw, kl, rkc, rvc, A, k0, P.m_c, P.m_c, stride, 1, 0, sl2, lane);
@@ -883,7 +949,7 @@ __device__ void standard_block(const PartialsParams& P, int blk, int wave, int l
     stream_keys<D, NT, KV>(st, qw, kl, rkd, rvd, A, k0, len, len, stride, P.ntok, 0, sl2, lane);
   }
   __syncthreads();  // the merge buffer overlays the waves' K tiles
-  merge_waves<D, NT>(st, merge_lds, wave, lane);
+  merge_waves(st, merge_lds, wave, lane);
   const float vs = P.v_scale ? P.v_scale[gam] : 1.f;
   const float* acc_s = merge_lds;
   const float* l_s = merge_lds + ROWS * LD + ROWS;
@@ -1022,7 +1088,7 @@ __device__ __forceinline__ void ctx_large_body(const PartialsParams& P) {
   auto step = [&](int key, int buf, Stage& spare, Stage& next, bool stage_next) {
     fetch(spare, key + 3 * T);
     if (rows)
-      tile_update<D, 1>(st, [&](int a, int ss) { return slot(buf, a * KS + ss)[lane]; },
+      tile_update(st, [&](int a, int ss) { return slot(buf, a * KS + ss)[lane]; },
                         [&](int t) { return slot(buf, KOPS + t)[lane]; },
                         [&](int, int ss) { return qop[0][ss]; }, nkeys - key, 1, 0,
                         scale_log2, lane);
