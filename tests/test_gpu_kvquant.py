@@ -11,6 +11,7 @@ import workloads
 from .gpu_util import run_decode, run_replicated, to_device
 from .parity import assert_parity, value_units
 from .pins_kvquant import KVS, code_table, elements, fill_code, stored
+from .test_gpu_switch import run_path
 
 pytestmark = pytest.mark.gpu
 
@@ -203,3 +204,38 @@ def test_generation_loop_with_codes(kv):
             got = out.cpu().double().numpy()
             _report(f"{kv} loop step {step}", *assert_parity(got, ref, f"{kv} loop step {step}", x=y))
         assert bif.bifattn_plan_status(plan) == bif.OK
+
+
+# b, h, g, d, m_c, m_d, n: one to four query tiles, key ranges that end one
+# short of, at and one past a 32-key tile, empty decode caches, several tokens.
+OFFSET_CASES = [
+    (3, 4, 2, 64, 31, 33, 1),
+    (4, 16, 4, 128, 32, 31, 2),
+    (4, 32, 1, 128, 33, 32, 1),
+    (2, 24, 1, 64, 65, 0, 1),
+    (3, 64, 1, 128, 97, 5, 1),
+]
+
+
+@pytest.mark.parametrize("path", ["standard", "bifurcated"])
+@pytest.mark.parametrize("case", OFFSET_CASES, ids=lambda c: "b%d_h%d_g%d_d%d_mc%d_md%d_n%d" % c)
+def test_int4_offset_leaves_the_result(case, path):
+    """The streaming waves hold int4 codes with 24 added. Queries whose
+    elements share a mean of 2 make the offset's part of a logit, 24 sum(q),
+    some hundred times the logit itself. Its fp32 sums are off by at most
+    d * 2^-24 * 24 sum|q| ~ 0.05, times scale * k_scale (< 0.06) 3e-3 in a
+    weight's exponent: a bound of the size of the weights' bf16 rounding, so
+    the usual gates hold. The scale keeps the logits as wide as a unit normal
+    query's."""
+    b, h, g, d, m_c, m_d, n = case
+    x = workloads.make_inputs(b, h, g, d, m_c, m_d, seed=960 + m_c, ragged=True, n=n, kv="int4")
+    if m_d >= n and b >= 3:
+        x["lens"][1], x["lens"][-1] = (0 if n == 1 else n), m_d
+    rng = np.random.default_rng(961 + m_c)
+    q = rng.standard_normal(x["q"].shape).astype(np.float32) + 2
+    x["q"] = workloads.f32_to_bf16_bits(q)
+    scale = 1 / np.sqrt(5 * d)
+    print(f"[case] int4 offset {case} {path} lens={x['lens'].tolist()}", flush=True)
+    out = run_path(x, path, scale=scale)
+    ref = oracle.attention(**x, scale=scale)
+    _report(f"int4 offset {case} {path}", *assert_parity(out, ref, f"int4 offset {case}", x=x))
