@@ -264,19 +264,21 @@ def summarize_profile(stats_dir: str, fetch_dir: str, write_dir: str, workload: 
 
 def algorithmic_read_bytes(workload: str, kernel: str):
     """(description, bytes) of the KV a kernel must read once for the
-    workload: the context chunk of every group for the many-row context
-    kernels, the valid decode rows for the decode launch of a many-row plan,
-    both for the few-row partial launch; None for unknown workloads."""
+    workload: the context chunk of every group for the many-row 16x16 context
+    kernel, the context and the valid decode rows for the launches that hold
+    both (the few-row partial launch, the 32x32 kernel's over units of at most
+    32 query rows); None for unknown workloads."""
     w = workloads.WORKLOADS.get(workload)
     if w is None:
         return None
     rb = workloads.row_bytes(w.d, w.kv)
     ctx = 2 * rb * w.g * w.m_c
-    if kernel in ("ctx_large", "ctx_wide"):
+    rows = w.h // w.g * w.n
+    if kernel == "ctx_large" or (kernel == "ctx_wide" and rows > 32):
         return "one copy of the context K and V", ctx
     lens = workloads.make_workload_lens(w)
     dec = 2 * rb * w.g * int(np.sum(lens, dtype=np.int64))
-    if w.b * (w.h // w.g) * w.n > 64:
+    if kernel == "partials" and w.b * rows > 64:
         return "every sample's valid decode K and V", dec
     return "one copy of the context K and V plus every sample's valid decode K and V", ctx + dec
 
@@ -474,16 +476,27 @@ def main():
     ctx_bytes = 2 * workloads.row_bytes(w.d, w.kv) * w.g * w.m_c
     dec_bytes = B_kv - ctx_bytes
     ctx_flops = 4 * w.h * w.n * w.d * w.b * w.m_c
-    if many_rows and (dec_us is None or ctx_us >= dec_us):
+    one_launch = many_rows and info["fused"] == 1  # then each of the three times is that launch's
+    if one_launch and B_kv / (HBM_PEAK_GBS * 1e9) > flops / (MFMA_PEAK_TFLOPS * 1e12):
+        # Context and decode work-groups in one launch, the bytes its higher roof.
+        gbs = B_kv / (ctx_us * 1e-6) / 1e9
+        roofline = {"kernel": "ctx_wide_kernel (many-row context and decode partials)",
+                    "bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS,
+                    "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4),
+                    "traffic": measured_traffic(w.name, "ctx_wide"),
+                    "avg_launch_us": round(ctx_us, 3), "bytes_per_launch": B_kv,
+                    "flops_per_launch": flops}
+    elif many_rows and (one_launch or dec_us is None or ctx_us >= dec_us):
         # The many-row context kernel: a contraction over b*p*n rows per group.
-        tflops = ctx_flops / (ctx_us * 1e-6) / 1e12
+        launch_flops = flops if one_launch else ctx_flops
+        tflops = launch_flops / (ctx_us * 1e-6) / 1e12
         ck = "ctx_wide" if info.get("ctx_kernel") == 2 else "ctx_large"
         roofline = {"kernel": f"{KERNEL_NAMES[ck]} (many-row context partials)", "bound": "mfma",
                     "achieved": round(tflops, 1), "peak": MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(tflops / MFMA_PEAK_TFLOPS, 4),
                     "traffic": measured_traffic(w.name, ck),
-                    "avg_launch_us": round(ctx_us, 3), "flops_per_launch": ctx_flops,
-                    "bytes_per_launch": ctx_bytes}
+                    "avg_launch_us": round(ctx_us, 3), "flops_per_launch": launch_flops,
+                    "bytes_per_launch": B_kv if one_launch else ctx_bytes}
     elif many_rows:
         gbs = dec_bytes / (dec_us * 1e-6) / 1e9
         roofline = {"kernel": "partials_kernel (decode partials)", "bound": "hbm",
