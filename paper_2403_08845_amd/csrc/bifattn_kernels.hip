@@ -250,7 +250,9 @@ struct KvInt4 : KvBits<4> {
 // the value is code + 24, exactly, at one shift and one v_bitop3 for two codes.
 // The constant leaves the logits through their first accumulator (-24 sum(q))
 // and the weighted values through the sum of the rounded weights. Nibble t of
-// a word pairs with nibble t + 4, so Q^T operands take the same order.
+// a word pairs with nibble t + 4, so Q^T operands take the same order. 32 samples
+// of an MHA layer over 8k: 34.6 -> 30.9 us per step, the error against 64 bits
+// 1.54e-3 either way.
 constexpr float kInt4Offset = 24.f;
 __device__ __forceinline__ uint32_t int4_pair(uint32_t w, int t) {  // nibbles t and t + 4
   const uint32_t x = t == 0 ? w << 3 : w >> (4 * t - 3);
@@ -1170,6 +1172,9 @@ ctx_large_kernel(PartialsParams P) {
 // the lanes that fill padding load from beyond the buffer's range, which
 // writes zeros without a memory access. One barrier per stage hands a
 // filled buffer to every wave and releases the oldest for refilling.
+// Against waves of 16 rows (us per step): d = 64, b 64, h 16, g 4, m_c 4097,
+// ragged, 31-45 -> 13.0; against four query tiles per streaming wave: b 16,
+// h 32, g 8, m_c 3001 (64 rows per group) 21.6 -> 13.9.
 template <int D> struct Wide {
   static constexpr int RB = D * 2;          // bytes per bf16 row
   static constexpr int KSTEPS = D / 16;     // k-steps of the logits
@@ -1552,7 +1557,12 @@ __device__ __forceinline__ void ctx_wide_block(const PartialsParams& P, unsigned
 }
 
 // Grid: n_ctx_blocks context work-groups, then one work-group for every
-// NW / 4 of the n_dec_blocks decode work-groups, whose waves are independent.
+// NW / 4 of the n_dec_blocks decode work-groups, whose waves are independent:
+// the context part is bound by its chain of products and softmax, the decode
+// part by HBM, and the dispatcher fills the slots the context part leaves.
+// Against a launch behind it or on a second stream (us per step): MQA, 128
+// samples over 16k, 65.2 -> 56.7; 4 draft tokens, 32 samples over 8k, 94.5 ->
+// 81.4; ragged GQA, 256 samples over 32k, 221.6 -> 216.9.
 template <int D, int NW, int NB, int SK, typename KV, int NTD>
 __device__ __forceinline__ void ctx_wide_body(const PartialsParams& P) {
   constexpr int QB = NTD * (D / 32) * 64 * 16;  // bytes of a decode wave's Q^T operands
@@ -1634,7 +1644,9 @@ constexpr bool fits_two_waves() {
 // constant lane offset), each summed by its own lanes in a fixed order, the
 // sums added across them at the end; NL loads are issued ahead, together with
 // the statistics. Bound by the memory round trip and, on MQA and GQA, by the
-// partials' bytes. The group's value scale
+// partials' bytes: against loads of 8 bytes a lane and one row each, ragged GQA
+// (256 samples over 32k) 10.2 -> 8.9 us, and a step with 51 partials a row (b 20,
+// h 32, g 1, m_c 3000) 27.4 -> 26.6 us. The group's value scale
 // multiplies the result (every partial of the row shares it); the first row
 // of each group checks that the group's scales are positive normal floats.
 template <int D, int NL>
