@@ -1681,7 +1681,8 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineParams C) {
     const int k1 = min(k0 + 64, np);
     // The chunk's loads: nc of context partials [k0, ce), then of decode
     // partials [d0, k1). In a last, partly filled load the spare lanes repeat
-    // the load's first partial and weigh it 0.
+    // the load's first partial and leave it out of their sum (a weight of 0
+    // would not do: the partial of an infinite value is infinite).
     const int ce = min(k1, C.S_c), d0 = max(k0, C.S_c);
     const int nc = k0 < ce ? (ce - k0 + PPL - 1) / PPL : 0;
     const int nl = nc + (d0 < k1 ? (k1 - d0 + PPL - 1) / PPL : 0);
@@ -1723,9 +1724,14 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineParams C) {
 #pragma unroll
       for (int u = 0; u < NL; ++u) {
         const int l = l0 + u;
-        const int kk = (l < nc ? k0 + l * PPL : d0 + (l - nc) * PPL) + sub;
-        const float wu = __shfl(w, min(kk - k0, 63));
-        if (l < nl) acc += v[u] * (kk < (l < nc ? ce : k1) ? wu : 0.f);
+        const int kf = l < nc ? k0 + l * PPL : d0 + (l - nc) * PPL;  // the load's first partial
+        const int kend = l < nc ? ce : k1;
+        const float wu = __shfl(w, min(kf + sub - k0, 63));
+        if (l < nl) {
+          const bool own = kf + sub < kend;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[e] += (own ? v[u][e] : 0.f) * wu;
+        }
       }
     }
   }
