@@ -251,8 +251,8 @@ struct KvInt4 : KvBits<4> {
 // The constant leaves the logits through their first accumulator (-24 sum(q))
 // and the weighted values through the sum of the rounded weights. Nibble t of
 // a word pairs with nibble t + 4, so Q^T operands take the same order. 32 samples
-// of an MHA layer over 8k: 34.6 -> 30.9 us per step, the error against 64 bits
-// 1.54e-3 either way.
+// of an MHA layer over 8k: 34.6 -> 30.9 us per step; the error against 64 bits is
+// that of converted codes to about 0.1% of itself, from 512 keys to 2^20.
 constexpr float kInt4Offset = 24.f;
 __device__ __forceinline__ uint32_t int4_pair(uint32_t w, int t) {  // nibbles t and t + 4
   const uint32_t x = t == 0 ? w << 3 : w >> (4 * t - 3);
@@ -311,10 +311,10 @@ __device__ __forceinline__ int qk_key(int a, int r) { return 16 * a + 4 * (r & 3
 // lacc holds the row's sum of the bf16-rounded weights (the weights the
 // values are multiplied by) in all four of its elements, instead of the
 // lane's share of the fp32 weights in l.
-// With OFF (int4 caches of the streaming waves, see Int4Offset) the operands
+// With OFF (int4 caches of the streaming waves, see kInt4Offset) the operands
 // hold each code's value plus an offset: bias starts every logit at minus the
 // offset's share, and lacc's sums of the rounded weights take it out of acc
-// at the end.
+// at the end and every kOffsetTiles tiles (take_offset).
 template <int D, int NT, bool MS = false, bool OFF = false> struct RowState {
   static constexpr int DV = D / 16;
   static constexpr bool kSums = MS || OFF;  // sums of the rounded weights by the matrix cores
@@ -617,6 +617,24 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const uint8_t* base,
                                            0x00020000);
 }
 
+// Take the int4 offset of the tiles since the last time out of the values.
+// Once at the end would do but for the rounding: acc holds 24 times the sum of
+// the weights, which grows with the keys while the weighted values grow with
+// their square root. Over 2^18 keys of a wave the error against 64 bits was
+// 7e-3 to 2.1e-2 instead of 1.6e-3; every 2^9 keys it is 1.6e-3 again (waves of
+// few-row plans rarely hold more).
+constexpr int kOffsetTiles = 16;
+template <int D, int NT, bool OFF>
+__device__ __forceinline__ void take_offset(RowState<D, NT, false, OFF>& st) {
+  static_assert(OFF, "only states with an offset");
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+    for (int t = 0; t < D / 16; ++t) st.acc[nt][t] -= kInt4Offset * st.lacc[nt];
+    st.lacc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+}
+
 // Row totals of the per-lane sums (the four lanes of a row share the row).
 template <int D, int NT, bool MS, bool OFF>
 __device__ __forceinline__ void finish_sums(RowState<D, NT, MS, OFF>& st) {
@@ -626,10 +644,8 @@ __device__ __forceinline__ void finish_sums(RowState<D, NT, MS, OFF>& st) {
       st.l[nt] = st.lacc[nt][0];
     else
       st.l[nt] = xor32_sum(xor16_sum(st.l[nt]));
-    if constexpr (OFF)
-#pragma unroll
-      for (int t = 0; t < D / 16; ++t) st.acc[nt][t] -= kInt4Offset * st.lacc[nt];
   }
+  if constexpr (OFF) take_offset(st);
 }
 
 // Write the wave's partials of rows row0 + nt*16 + n < nrows: lane (n, G)
@@ -708,23 +724,31 @@ __device__ __forceinline__ void stream_keys(StreamState<D, NT, KV>& st, const u3
   // Prefetches are unconditional: past the resource range the buffer load
   // returns zeros without a memory access, and a fixed count of loads in
   // flight lets each wait cover only the tile being consumed.
-  for (int key = k0;; key += 2 * stride) {
-    const int key1 = key + stride;
-    B.template load<AUX>(rk, rv, key1, lane);
-    const int nv0 = min(kTileKeys, k1 - key);
-    if (nv0 < kTileKeys) A.mask_v(nv0, lane);
-    A.stage_k(kl, lane);
-    tile_update(st, k_at, [&](int t) { return A.vop(t); }, q_at, kend - key, ntok,
-                       vis0 - key, scale_log2, lane);
-    if (key1 >= k1) break;
-    const int key2 = key1 + stride;
-    A.template load<AUX>(rk, rv, key2, lane);
-    const int nv1 = min(kTileKeys, k1 - key1);
-    if (nv1 < kTileKeys) B.mask_v(nv1, lane);
-    B.stage_k(kl, lane);
-    tile_update(st, k_at, [&](int t) { return B.vop(t); }, q_at, kend - key1, ntok,
-                       vis0 - key1, scale_log2, lane);
-    if (key2 >= k1) break;
+  // int4: the offset is taken out after every kOffsetTiles tiles. That many are
+  // an even number, so the first tile past them is in A when their loop ends.
+  for (int end = k1;; k0 = end) {
+    if constexpr (KV::BITS == 4)
+      end = (k1 - k0) / stride > kOffsetTiles ? k0 + kOffsetTiles * stride : k1;
+    for (int key = k0;; key += 2 * stride) {
+      const int key1 = key + stride;
+      B.template load<AUX>(rk, rv, key1, lane);
+      const int nv0 = min(kTileKeys, k1 - key);
+      if (nv0 < kTileKeys) A.mask_v(nv0, lane);
+      A.stage_k(kl, lane);
+      tile_update(st, k_at, [&](int t) { return A.vop(t); }, q_at, kend - key, ntok,
+                  vis0 - key, scale_log2, lane);
+      if (key1 >= end) break;
+      const int key2 = key1 + stride;
+      A.template load<AUX>(rk, rv, key2, lane);
+      const int nv1 = min(kTileKeys, k1 - key1);
+      if (nv1 < kTileKeys) B.mask_v(nv1, lane);
+      B.stage_k(kl, lane);
+      tile_update(st, k_at, [&](int t) { return B.vop(t); }, q_at, kend - key1, ntok,
+                  vis0 - key1, scale_log2, lane);
+      if (key2 >= end) break;
+    }
+    if (end == k1) break;
+    if constexpr (KV::BITS == 4) take_offset(st);
   }
 }
 

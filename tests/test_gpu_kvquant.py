@@ -239,3 +239,22 @@ def test_int4_offset_leaves_the_result(case, path):
     out = run_path(x, path, scale=scale)
     ref = oracle.attention(**x, scale=scale)
     _report(f"int4 offset {case} {path}", *assert_parity(out, ref, f"int4 offset {case}", x=x))
+
+
+@pytest.mark.parametrize("path,m_c", [("standard", 1 << 20), ("standard", 300001),
+                                      ("bifurcated", 1 << 20)])
+def test_int4_offset_over_long_contexts(path, m_c):
+    """A wave's sums of weighted values hold 24 per unit of weight until the
+    offset is taken out. With 2^18 keys to a wave (a standard path's quarter
+    of 2^20) and an fp32 accumulator that keeps the offset to the end, the sum
+    is 24 * 2^18 weights against the ~2^9 * 1.6 of the values' own: its
+    roundings come to 1e-2 of the result. With the offset taken out every 2^9
+    keys they stay below 1e-4, so the bound is the bf16 rounding of the
+    weights: 2^-9 / sqrt(3) on average, 1.7e-3 measured, 2.5e-3 allowed."""
+    b, h, g, d, m_d = 1, 4, 1, 64, 32
+    x = workloads.make_inputs(b, h, g, d, m_c, m_d, seed=970, kv="int4")
+    out = run_path(x, path)
+    ref = oracle.attention(**x)
+    max_abs, rel = assert_parity(out, ref, f"int4 {path} {m_c}", x=x)
+    _report(f"int4 {path} {m_c}", max_abs, rel)
+    assert rel <= 2.5e-3, rel
