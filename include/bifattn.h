@@ -324,7 +324,8 @@ bifattn_status_t bifattn_plan_read_timing(bifattn_plan_t plan, int32_t *calls, d
  * enqueued) when the problem's workspace exceeds the scratch buffer: it
  * holds g*S_c*b*(h/g)*n context partials and b*g*S_d*4*(h/g)*n decode
  * partials of (d + 2)*4 bytes each (S_c context splits and S_d decode
- * chunks of the work split without a side stream), about 4.3 MB for the
+ * chunks of the work split without a side stream; a problem that does not fit
+ * takes longer chunks if it fits with those), about 4.3 MB for the
  * 32-sample 7B-shaped MHA layer and 51 MB for the 256-sample GQA layer over
  * a 32k context. The size check comes before any HIP call.
  */

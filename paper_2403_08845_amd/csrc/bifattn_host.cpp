@@ -207,8 +207,8 @@ int seq_keys(int64_t units, int64_t rows, int start) {
 
 // allow_fork: the many-row path may run the decode launch on the plan's own
 // stream (off for the allocation-free entry point, which owns no stream).
-// coarse: the longest chunks (the allocation-free entry point's limit counts
-// these, and it takes them where shorter ones' partials pass the scratch).
+// coarse: the longest chunks (the allocation-free entry point takes them where
+// the partials of the usual ones pass its scratch).
 bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coarse = false) {
   const bifattn_dims_t& d = P->dims;
   P->ntok = d.n > 0 ? d.n : 1;
@@ -297,7 +297,7 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
     P->ctx_wide = wide ? split.waves : 0;
     const int block_rows = wide ? 32 * P->ctx_wide : kLargeRowsPerBlock;
     P->ctx_row_blocks = (int)ceil_div(M, block_rows);
-    int key_step = wide ? 64 : kTileKeys;  // keys per stage of the kernel's loop
+    const int key_step = wide ? 64 : kTileKeys;  // keys per stage of the kernel's loop
     if (!one_launch || wgs > 0) {
       // With the decode work-groups in a launch of their own: about one
       // work-group per CU for eight-wave work-groups, two for four-wave ones;
@@ -307,10 +307,7 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
                                  : (P->ctx_wide == 8 ? kCUs : 2 * kCUs);
       split.splits = ceil_div(wgs > 0 ? wgs : target, (int64_t)d.g * P->ctx_row_blocks);
     }
-    if (coarse && !both) {
-      split.splits = ceil_div(2 * kCUs, d.g * ceil_div(M, kLargeRowsPerBlock));
-      key_step = kTileKeys;
-    }
+    if (coarse && !both) split.splits = ceil_div(2 * kCUs, d.g * ceil_div(M, kLargeRowsPerBlock));
     const int64_t splits = std::max<int64_t>(1, split.splits);
     int64_t ck = round_up(ceil_div(d.m_c, splits), ck_step(key_step, d.m_c, splits));
     if (coarse && M <= 64) ck = long_keys;
@@ -828,9 +825,8 @@ bifattn_status_t bifattn_decode_noalloc(const bifattn_dims_t* dims, const void* 
   st = plan_splits(&P, false);
   if (st != BIFATTN_OK) return st;
   WorkspaceLayout L = workspace_layout(&P, false);
-  if (L.bytes > kScratchBytes / 16) {
-    // Which problems fit is a matter of the longest chunks, which differ
-    // from these by well under that factor.
+  if (L.bytes > kScratchBytes) {
+    // Longer chunks leave fewer partials.
     bifattn_plan_s Q;
     Q.dims = P.dims;
     Q.scale = P.scale;
@@ -838,10 +834,8 @@ bifattn_status_t bifattn_decode_noalloc(const bifattn_dims_t* dims, const void* 
     if (st != BIFATTN_OK) return st;
     const WorkspaceLayout Lq = workspace_layout(&Q, false);
     if (Lq.bytes > kScratchBytes) return BIFATTN_ESCRATCH;
-    if (L.bytes > kScratchBytes) {
-      P = Q;
-      L = Lq;
-    }
+    P = Q;
+    L = Lq;
   }
   if (hipGetDevice(&P.device) != hipSuccess) {
     (void)hipGetLastError();

@@ -1,6 +1,6 @@
 """Work splits of few-row plans that leave part of the GPU idle: shorter
 context and decode chunks, against the oracle; and which problems the
-allocation-free entry point takes, which does not depend on them."""
+allocation-free entry point takes: those whose partials fit its scratch."""
 import ctypes
 import random
 
@@ -34,10 +34,19 @@ def _coarse_bytes(b, h, g, d, m_c, m_d):
     return 256 * _ceil(off + 4, 256)
 
 
-def test_noalloc_takes_the_problems_whose_longest_chunks_fit():
-    L = bif.lib()
-    rng = random.Random(4)
+def _noalloc_status(b, h, g, d, m_c, m_d, n=1, kv="bf16"):
+    """Status of an allocation-free call with an unaligned pointer: ESCRATCH, or
+    for a problem that fits whatever the later argument checks say."""
     fake = ctypes.c_void_p(256)
+    dims = bif.noalloc_dims(b, h, g, d, m_c, m_d, n=n, kv=kv, path="bifurcated")
+    return bif.lib().bifattn_decode_noalloc(ctypes.byref(dims), ctypes.c_void_p(8), fake, fake,
+                                            fake, fake, fake, None, None, fake, None)
+
+
+def test_noalloc_takes_the_problems_whose_longest_chunks_fit():
+    """What fits with the longest chunks is taken whatever the plan's own; of
+    few-row plans, whose own chunks are no longer, nothing else is."""
+    rng = random.Random(4)
     seen = {True: 0, False: 0}
     for _ in range(4000):
         p = rng.choice((1, 2, 4, 8))
@@ -51,14 +60,30 @@ def test_noalloc_takes_the_problems_whose_longest_chunks_fit():
         need = _coarse_bytes(b, g * p, g, d, m_c, m_d)
         if not (40 << 20) < need < (90 << 20):
             continue
-        dims = bif.noalloc_dims(b, g * p, g, d, m_c, m_d, path="bifurcated")
-        # an unaligned pointer: a problem that fits goes no further than the argument checks
-        st = L.bifattn_decode_noalloc(ctypes.byref(dims), ctypes.c_void_p(8), fake, fake, fake,
-                                      fake, fake, None, None, fake, None)
+        st = _noalloc_status(b, g * p, g, d, m_c, m_d)
         fits = need <= bif.NOALLOC_SCRATCH_BYTES
-        assert (st == bif.ESCRATCH) == (not fits), (b, g, p, d, m_c, m_d, need, st)
+        if fits or b * p <= 32:
+            assert (st == bif.ESCRATCH) == (not fits), (b, g, p, d, m_c, m_d, need, st)
         seen[fits] += 1
     assert min(seen.values()) > 20, seen
+
+
+@pytest.mark.parametrize("case", [
+    # b, h, g, d, m_c, m_d, n, kv: two thirds of the scratch or less with the
+    # plan's own chunks, more than all of it with others that nothing would run
+    (64, 169, 169, 128, 37728, 112, 1, "int4"),
+    (187, 61, 61, 128, 1382, 14, 2, "int8"),
+    (1491, 6, 3, 128, 856, 30, 2, "bf16"),
+    (60, 720, 180, 64, 816, 116, 1, "bf16"),
+    (37, 400, 400, 64, 42654, 0, 1, "fp8_e4m3"),
+], ids=lambda c: "b%d_h%d_g%d_d%d_mc%d_md%d_n%d_%s" % c)
+def test_noalloc_takes_a_problem_that_fits(case):
+    assert _noalloc_status(*case) != bif.ESCRATCH
+
+
+def test_noalloc_refuses_what_cannot_fit():
+    # the outputs' own partials: 64 rows of 4000 groups, one split, four decode waves
+    assert _noalloc_status(64, 4000, 4000, 128, 100, 100) == bif.ESCRATCH
 
 
 @pytest.mark.gpu
