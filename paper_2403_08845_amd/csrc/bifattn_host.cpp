@@ -674,7 +674,7 @@ bifattn_status_t bifattn_plan_get_info(bifattn_plan_t P, bifattn_plan_info_t* in
   info->path = P->path;
   info->workspace_bytes = P->ws_bytes;
   info->ctx_kernel = P->ctx_mode != kCtxLarge ? 0 : (P->ctx_wide ? 2 : 1);
-  info->side_stream = P->fork;
+  info->side_stream = P->fork && !P->fused;
   return BIFATTN_OK;
 }
 

@@ -1,6 +1,6 @@
 """bifattn_decode captured in a HIP graph (torch.cuda.graph) and replayed: a
-call enqueues only kernel launches (and, on the two-stream many-row path, an
-event fork and join), no memory set or copy, so a serving loop can capture a
+call enqueues only kernel launches (and, where the decode part runs on the
+plan's side stream, an event fork and join), no memory set or copy, so a serving loop can capture a
 decode step once and replay it. Every replay, with eager work and
 synchronisations in between, equals the eager call bit for bit (MI355X only)."""
 import numpy as np
@@ -15,7 +15,10 @@ pytestmark = pytest.mark.gpu
 
 # b, h, g, d, m_c, m_d_max, n, kv, fork: the standard path (tiny layer), the
 # fused few-row launch, the many-row context kernel then the decode launch,
-# the two-stream many-row path, several tokens, an 8-bit cache with scales.
+# both in one launch, several tokens, an 8-bit cache with scales; and the side
+# stream (units of more than 32 query rows), which takes eight- and four-wave
+# work-groups, the kernel of 16-row waves (below 128 rows per group), codes, and
+# d = 64.
 CASES = [
     (4, 4, 4, 64, 128, 16, 1, "bf16", None),
     (8, 32, 32, 128, 2048, 256, 1, "bf16", None),
@@ -23,6 +26,11 @@ CASES = [
     (40, 32, 1, 128, 2000, 64, 1, "bf16", "1"),
     (8, 32, 32, 128, 900, 120, 4, "bf16", "1"),
     (16, 32, 8, 128, 1500, 100, 1, "fp8_e4m3", None),
+    (8, 40, 1, 128, 2000, 64, 1, "bf16", "1"),
+    (4, 96, 2, 128, 1500, 200, 1, "bf16", "1"),
+    (2, 40, 1, 128, 1500, 200, 1, "bf16", "1"),
+    (6, 36, 2, 128, 2000, 100, 2, "int4", "1"),
+    (8, 40, 1, 64, 2000, 64, 1, "int8", "1"),
 ]
 
 
@@ -35,7 +43,11 @@ def test_graph_replays_equal_the_eager_call(case, monkeypatch):
     x = workloads.make_inputs(b, h, g, d, m_c, m_d, seed=1600 + m_c, ragged=True, n=n, kv=kv)
     y = workloads.make_inputs(b, h, g, d, m_c, m_d, seed=1601 + m_c, ragged=True, n=n, kv=kv)
     with bif.Plan(*dims_of(x), n=tokens_of(x), kv=kv_of(x)) as plan:
-        print(f"[case] graph {case} plan={plan.info()}", flush=True)
+        info = plan.info()
+        print(f"[case] graph {case} plan={info}", flush=True)
+        if fork is not None and b * (h // g) * n > 32:
+            assert info["side_stream"] == (fork == "1" and h // g * n > 32)
+            assert info["fused"] == (fork == "1" and h // g * n <= 32)
         dev, devy = to_device(x), to_device(y)
 
         def call(v, out):

@@ -2,8 +2,9 @@
 
 * nothing is written outside `out` and, for the append, outside the rows it
   owns: canary bytes around the output and the decode caches are unchanged
-  after every path (few-row fused launch, many-row context with and without
-  the side-stream decode launch, standard path, replicated ablation, append);
+  after every path (few-row fused launch, many-row context with the decode
+  part in its launch, behind it and on the side stream, standard path,
+  replicated ablation, append);
 * a plan's destroy and set_timing wait for the plan's own work only, not for
   unrelated work on other streams of the device.
 """
@@ -49,8 +50,10 @@ def _guarded_cache(a, kv):
 # (b, h, g, d, m_c, m_d, n, kv, path, fork): every launch structure of a call
 CASES = [
     (6, 16, 4, 128, 700, 90, 1, "bf16", "bifurcated", None),   # few-row fused launch
-    (40, 32, 1, 128, 1000, 64, 1, "bf16", "bifurcated", "0"),  # many-row, one stream
-    (40, 32, 1, 128, 1000, 64, 1, "bf16", "bifurcated", "1"),  # many-row, side stream
+    (40, 32, 1, 128, 1000, 64, 1, "bf16", "bifurcated", "0"),  # many-row, two launches
+    (40, 32, 1, 128, 1000, 64, 1, "bf16", "bifurcated", "1"),  # many-row, one launch
+    (8, 40, 1, 128, 1000, 64, 1, "bf16", "bifurcated", "1"),   # many-row, side stream
+    (8, 80, 2, 64, 1000, 64, 1, "int8", "bifurcated", "1"),
     (8, 32, 32, 128, 600, 120, 4, "fp8_e4m3", "bifurcated", None),
     (5, 16, 4, 64, 300, 40, 1, "int8", "standard", None),      # standard path
     (40, 32, 1, 128, 1000, 64, 2, "int4", "bifurcated", "1"),  # int4 many-row, side stream
@@ -76,6 +79,8 @@ def test_canaries_around_output_and_caches(case, monkeypatch):
     vs = None if x.get("v_scale") is None else torch.from_numpy(x["v_scale"]).cuda()
     print(f"[case] canaries {case}", flush=True)
     with bif.Plan(b, h, g, d, m_c, m_d, n=n, kv=kv, path=path) as plan:
+        if fork is not None:  # units of at most 32 query rows take one launch instead
+            assert plan.info()["side_stream"] == (fork == "1" and h // g * n > 32)
         bif.bifattn_decode_scaled(plan, dev["q"], dev["Kc"], dev["Vc"], Kd, Vd, lens, ks, vs, out)
         assert bif.bifattn_plan_status(plan) == bif.OK
         _intact(ob, nout, "out")

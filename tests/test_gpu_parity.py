@@ -267,27 +267,37 @@ def test_draft_tokens_masked_tail_and_replicated():
     assert_parity(run_replicated(x), oracle.attention(**x), "replicated, n = 4", x=x)
 
 
-@pytest.mark.parametrize("case", [(40, 32, 1, 128, 2000, 64, 1), (6, 32, 2, 128, 700, 40, 1),
-                                  (8, 32, 32, 128, 900, 120, 4)],
-                         ids=lambda c: "b%d_h%d_g%d_d%d_mc%d_md%d_n%d" % c)
+@pytest.mark.parametrize("case", [(40, 32, 1, 128, 2000, 64, 1, "bf16"),
+                                  (6, 32, 2, 128, 700, 40, 1, "bf16"),
+                                  (8, 32, 32, 128, 900, 120, 4, "bf16"),
+                                  # units of more than 32 query rows
+                                  (8, 40, 1, 128, 2000, 300, 1, "bf16"),
+                                  (4, 96, 2, 128, 900, 120, 1, "fp8_e4m3"),
+                                  (5, 32, 2, 128, 1300, 77, 4, "int4"),
+                                  (9, 34, 1, 64, 1700, 130, 1, "bf16"),
+                                  (3, 63, 1, 64, 800, 64, 1, "int8")],
+                         ids=lambda c: "b%d_h%d_g%d_d%d_mc%d_md%d_n%d_%s" % c)
 def test_side_stream_decode(case, monkeypatch):
-    """Many-row plans may run the decode launch on a side stream beside the
-    context kernel (the call's stream waits for it before the combine):
-    forced on and off with either context kernel, every output matches the
-    oracle, and with the same kernel the two are bitwise equal when the plans
-    split the context alike."""
-    b, h, g, d, m_c, m_d, n = case
-    x = workloads.make_inputs(b, h, g, d, m_c, m_d, seed=1200 + m_c, ragged=True, n=n)
+    """Many-row plans may run the decode work-groups beside the context ones:
+    in the 32x32 kernel's launch for units of at most 32 query rows, else on a
+    side stream (the call's stream waits for it before the combine). Forced on
+    and off with either context kernel, every output matches the oracle, and
+    with the same kernel the two are bitwise equal when the plans split the
+    context alike."""
+    b, h, g, d, m_c, m_d, n, kv = case
+    x = workloads.make_inputs(b, h, g, d, m_c, m_d, seed=1200 + m_c, ragged=True, n=n, kv=kv)
     ref = oracle.attention(**x)
-    for wide in ("0", "1"):
+    for wide in ("0", "1") if d == 128 else ("1",):
         monkeypatch.setenv("BIFATTN_CTX_WIDE", wide)
         runs = []
         for fork in ("0", "1"):
             monkeypatch.setenv("BIFATTN_FORK", fork)
-            with bif.Plan(b, h, g, d, m_c, m_d, n=n) as plan:
+            with bif.Plan(b, h, g, d, m_c, m_d, n=n, kv=kv) as plan:
                 info = plan.info()
                 if b * (h // g) * n > 64:  # many rows per group (else the few-row launch)
-                    assert info["side_stream"] == int(fork)
+                    one_launch = wide == "1" and h // g * n <= 32
+                    assert info["side_stream"] == int(fork == "1" and not one_launch)
+                    assert info["fused"] == int(fork == "1" and one_launch)
                     assert info["ctx_kernel"] == (2 if wide == "1" else 1)
                 out = run_decode(x, plan=plan)
             _report(f"side stream {case} wide={wide} fork={fork}",
@@ -298,20 +308,28 @@ def test_side_stream_decode(case, monkeypatch):
 
 
 def test_plan_rule_for_large_decode_parts(monkeypatch):
-    """Without overrides, a many-row plan whose decode part is large takes the
-    side stream; with 256 or more rows per group it keeps the eight-wave 32x32
-    context kernel on five eighths of the CUs, with 128 to 255 rows its
-    four-wave form on about one work-group per CU."""
+    """Without overrides, a many-row plan whose decode part is large runs it beside
+    the 32x32 context kernel and leaves it part of the GPU: in one launch where
+    units have at most 32 query rows; else on the side stream, with the context
+    on five eighths of the CUs from 256 rows per group and on about one
+    four-wave work-group per CU with 128 to 255."""
     for var in ("BIFATTN_FORK", "BIFATTN_CTX_WIDE", "BIFATTN_CTX_WGS"):
         monkeypatch.delenv(var, raising=False)
     with bif.Plan(256, 32, 8, 128, 32768, 1024) as plan:  # 1024 rows per group
         info = plan.info()
-        assert info["side_stream"] == 1 and info["ctx_kernel"] == 2
+        assert info["fused"] == 1 and info["side_stream"] == 0 and info["ctx_kernel"] == 2
         assert info["ctx_blocks"] <= 160
     with bif.Plan(32, 32, 32, 128, 8192, 512, n=4) as plan:  # 128 rows per group
         info = plan.info()
-        assert info["side_stream"] == 1 and info["ctx_kernel"] == 2
+        assert info["fused"] == 1 and info["side_stream"] == 0 and info["ctx_kernel"] == 2
         assert info["ctx_blocks"] <= 256
+    for b, blocks in ((8, 160), (4, 256)):  # 40 rows per unit: 320 and 160 per group
+        with bif.Plan(b, 1280, 32, 128, 4096, 1024) as plan:
+            info = plan.info()
+            assert info["fused"] == 0 and info["side_stream"] == 1 and info["ctx_kernel"] == 2
+            assert info["ctx_blocks"] < blocks + 32 * info["ctx_row_blocks"]  # rounded up to splits
+    with bif.Plan(8, 1280, 32, 128, 4096, 16) as plan:  # a small decode part follows
+        assert plan.info()["fused"] == plan.info()["side_stream"] == 0
 
 
 def test_largest_context_rows_are_addressed():
