@@ -728,7 +728,7 @@ __device__ __forceinline__ void stream_keys(StreamState<D, NT, KV>& st, const u3
   // an even number, so the first tile past them is in A when their loop ends.
   for (int end = k1;; k0 = end) {
     if constexpr (KV::BITS == 4)
-      end = (k1 - k0) / stride > kOffsetTiles ? k0 + kOffsetTiles * stride : k1;
+      end = k1 - k0 > (int64_t)kOffsetTiles * stride ? k0 + kOffsetTiles * stride : k1;
     for (int key = k0;; key += 2 * stride) {
       const int key1 = key + stride;
       B.template load<AUX>(rk, rv, key1, lane);
