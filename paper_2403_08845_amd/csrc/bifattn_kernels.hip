@@ -1768,6 +1768,33 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineParams C) {
   if (sub == 0) *reinterpret_cast<f32x4*>(C.out + (size_t)row * D + col) = acc * inv;
 }
 
+// The combine of rows with one partial, a context's one split without decode
+// rows: PPL rows per wave. Bound by the rate at which waves start: 148 samples,
+// h 1024, d 128 57 us with a wave per row (whose spare lanes do nothing), 47 with
+// a wave per row and half the bytes per lane, 24 here.
+template <int D> __global__ __launch_bounds__(256) void combine_one_kernel(CombineParams C) {
+  constexpr int LPR = D / 4;
+  constexpr int PPL = 64 / LPR;
+  const int lane = threadIdx.x & 63, wave = wave_id();
+  const int col = 4 * (lane % LPR);
+  const int row = (blockIdx.x * 4 + wave) * PPL + lane / LPR;
+  if (row >= C.b * C.h) return;
+  const int i = row / C.h, j = row - i * C.h;
+  const int gam = j / C.p, jp = j - gam * C.p;
+  const size_t k = (size_t)gam * C.M + (size_t)i * C.p + jp;
+  const f32x4 acc = *reinterpret_cast<const f32x4*>(C.ctx_acc + k * D + col);
+  const float2 ml = C.ctx_ml[k];
+  const float vs = C.v_scale ? C.v_scale[gam] : 1.f;
+  if (i == 0 && jp == 0 && col == 0) {
+    const float ks = C.k_scale ? C.k_scale[gam] : 1.f;
+    const bool ok = ks >= __FLT_MIN__ && ks <= __FLT_MAX__ && vs >= __FLT_MIN__ && vs <= __FLT_MAX__;
+    if (!ok) atomicOr(C.status, kStatusScale);
+  }
+  const float w = exp2_fast(ml.x - (ml.x == kNegInf ? 0.f : ml.x));  // 1, or 0 of an empty one
+  const float inv = vs / (w * ml.y);
+  *reinterpret_cast<f32x4*>(C.out + (size_t)row * D + col) = acc * w * inv;
+}
+
 // One launch; with events, through hipExtLaunchKernel so that they carry the
 // kernel's own start and end.
 template <typename Prm>
@@ -2007,6 +2034,11 @@ hipError_t launch_partials(const PartialsParams& P, int d, int kv, int ctx_mode,
 hipError_t launch_combine(const CombineParams& C, int d, hipStream_t stream,
                           const LaunchEvents& ev) {
   const int rows = C.b * C.h;
+  if (C.S_c == 1 && C.S_d == 0 && !C.lens) {
+    if (d == 128) return launch(combine_one_kernel<128>, (rows + 7) / 8, 256, stream, ev, C);
+    if (d == 64) return launch(combine_one_kernel<64>, (rows + 15) / 16, 256, stream, ev, C);
+    return hipErrorInvalidValue;
+  }
   const int grid = (rows + 3) / 4;
   // The loads of a row's partials go out at once where there are at most 16
   // (one memory round trip), in the smallest of 4, 8 and 16 registers sets.

@@ -172,3 +172,39 @@ def test_many_rows_in_one_launch_equal_two(case, monkeypatch):
     run(lambda *a: bif.bifattn_decode_noalloc(dims, *a))
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
     assert_parity(outs[0].cpu().double().numpy(), oracle.attention(**x), str(case), x=x)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [
+    # b, h, g, d, m_c, n, kv: rows that fill the combine's work-groups or not,
+    # the smallest, the few-row and the many-row kernels
+    (1, 1, 1, 128, 1, 1, "bf16"),
+    (3, 5, 5, 64, 40, 1, "bf16"),
+    (7, 6, 2, 128, 50, 1, "int8"),
+    (9, 33, 1, 128, 64, 1, "bf16"),
+    (43, 24, 2, 64, 128, 2, "bf16"),
+    (77, 40, 1, 64, 100, 1, "int4"),
+    (1100, 33, 1, 64, 130, 1, "bf16"),   # many rows of units past 32: the estimated split
+], ids=lambda c: "b%d_h%d_g%d_d%d_mc%d_n%d_%s" % c)
+def test_one_partial_per_row(case):
+    """A context's one split without decode rows, whose combine has a kernel of
+    its own; a scale that is not positive is flagged there too."""
+    import torch
+    from .gpu_util import to_device
+    b, h, g, d, m_c, n, kv = case
+    x = workloads.make_inputs(b, h, g, d, m_c, 0, seed=2500 + m_c, n=n, kv=kv)
+    dev = to_device(x)
+    with bif.Plan(b, h, g, d, m_c, 0, n=n, kv=kv, path="bifurcated") as plan:
+        info = plan.info()
+        print(f"[case] {case} {info}", flush=True)
+        assert info["ctx_splits"] == 1 and info["dec_splits"] == 0
+        out = torch.full(tuple(x["q"].shape), float("nan"), dtype=torch.float32, device="cuda")
+        args = [dev[k] for k in ("q", "Kc", "Vc", "Kd", "Vd", "lens", "k_scale", "v_scale")]
+        bif.bifattn_decode_scaled(plan, *args, out)
+        assert bif.bifattn_plan_status(plan) == bif.OK
+        assert_parity(out.cpu().double().numpy(), oracle.attention(**x), str(case), x=x)
+        if kv != "bf16":
+            args[7] = args[7].clone()
+            args[7][-1] = 0.0
+            bif.bifattn_decode_scaled(plan, *args, out)
+            assert bif.bifattn_plan_status(plan) == bif.ESCALE
