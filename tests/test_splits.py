@@ -184,7 +184,7 @@ def test_many_rows_in_one_launch_equal_two(case, monkeypatch):
     (9, 33, 1, 128, 64, 1, "bf16"),
     (43, 24, 2, 64, 128, 2, "bf16"),
     (77, 40, 1, 64, 100, 1, "int4"),
-    (1100, 33, 1, 64, 130, 1, "bf16"),   # many rows of units past 32: the estimated split
+    (1100, 33, 1, 64, 64, 1, "bf16"),    # many rows, of units past 32
 ], ids=lambda c: "b%d_h%d_g%d_d%d_mc%d_n%d_%s" % c)
 def test_one_partial_per_row(case):
     """A context's one split without decode rows, whose combine has a kernel of
@@ -208,3 +208,14 @@ def test_one_partial_per_row(case):
             args[7][-1] = 0.0
             bif.bifattn_decode_scaled(plan, *args, out)
             assert bif.bifattn_plan_status(plan) == bif.ESCALE
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(1, 1536, 32, 128, 3079, 1024), (1, 512, 8, 128, 30000, 64),
+                                   (1, 2560, 64, 64, 1833, 512)])
+def test_four_query_tiles_leave_work_groups_for_the_decode_part(shape):
+    """With 33 to 64 query rows in one unit a work-group fills a CU: the chunks of
+    a step that fits the GPU leave an eighth of the CUs to the decode part."""
+    with bif.Plan(*shape) as plan:
+        info = plan.info()
+        assert info["ctx_kernel"] == 0 and info["ctx_blocks"] <= 224
