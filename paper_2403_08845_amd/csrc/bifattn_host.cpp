@@ -135,19 +135,20 @@ int ck_step(int key_step, int64_t m_c, int64_t splits) {
 // context work-groups, but each adds a partial of every query row for the
 // combine, and context work-groups beyond what the decode ones leave of the
 // GPU run behind others. Eight waves (256 rows) halve the reads of a key
-// chunk and of its work-groups there is one per CU; four (two per CU) overlap
-// one's start and end with the other's products, which wins on short contexts
-// (b 16, h 16, g 4, 4 tokens, m_c 3000: 16.3 us per step, eight 19.1; MQA over
-// 16k: 61.6, eight 56.3). The choice is the least of an estimate fitted to the
-// times of 62 MHA, GQA and MQA layers (32 to 4096 rows per group, 0.5k to 32k
-// keys) at about ten splits and both widths each; it is within 1.8% of the
-// best of those on average and 10% at worst:
-//   context work-group: 4.3 us + 18 ns per key (eight waves), 3.4 us + 19 ns
-//     (four), d = 64 0.59 of that per key; a sixth more as more than five
-//     eighths of the CUs run them (the clock gives way);
-//   decode work-group: 1.8 us + 1.6 us per 128 keys (d = 64: 0.6 us);
-//   the caches at 5.8 TB/s, the partials at 2.2 TB/s, and 2.4 us for each
-//     further batch of sixteen loads of the combine.
+// chunk and of its work-groups there is one per CU; four (two per CU, three
+// with d = 64: LDS and registers) overlap one's start and end with the
+// other's products, which wins on short contexts (b 16, h 16, g 4, 4 tokens,
+// m_c 3000: 16.3 us per step, eight 19.1; MQA over 16k: 61.6, eight 56.3).
+// The choice is the least of an estimate of the step's time. Its terms are the
+// parts of a step, but its constants are a fit of whole steps (1700 random
+// layers, 33 to 38400 rows per group, 0.2k to 40k keys, every cache type, at
+// about 24 settings each), not times of the parts. The chosen setting is 1.2%
+// slower than the best of those on average, 7% at the 95th percentile and 28%
+// at worst; the estimate plus 6 us is within 20% of the time of 19 steps in 20.
+// With two four-wave work-groups per CU counted for d = 64 too, decode work as
+// long for codes as for bf16, and a work-group that shares its CU as fast as
+// one alone, it was 2.6% and 42% (h = g = 40, d 64, m_c 12000, b 40: 35.3 us per
+// step, now 31.6; g 8, m_c 35226, 54 rows, no decode rows: 44.0, now 36.2).
 struct ManySplit {
   int waves = 4;
   int64_t splits = 1;
@@ -157,34 +158,43 @@ ManySplit many_row_split(const bifattn_plan_s* P, int64_t rows) {
   const bool half = d.d == 64;
   const int S_d = P->S_d;
   const double rows_all = (double)d.g * rows;
-  const double td = 1.8 + (half ? 0.6 : 1.6) * (double)ceil_div(std::min(P->dec_keys, d.m_d_max), 128);
+  const double codes = d.kv_type == BIFATTN_KV_BF16 ? 1.0 : d.kv_type == BIFATTN_KV_INT4 ? 0.54 : 0.61;
+  const double td =
+      1.75 + codes * (half ? 0.8 : 1.57) * (double)ceil_div(std::min(P->dec_keys, d.m_d_max), 128);
   const double stream = 2.0 * d.g * kv_row_bytes(d.d, d.kv_type) *
-                        ((double)d.m_c + 0.75 * (double)d.b * d.m_d_max) / 5.8e6;
+                        ((double)d.m_c + 0.75 * (double)d.b * d.m_d_max) / 5.84e6;
   ManySplit best;
   double least = 0.0;
   for (int waves = 4; waves <= (rows > 128 ? 8 : 4); waves += 4) {
-    const int slots = waves == 8 ? kCUs : 2 * kCUs;
+    const int slots = waves == 8 ? kCUs : (half ? 3 : 2) * kCUs;
     const int64_t per_split = (int64_t)d.g * ceil_div(rows, 32 * waves);
-    const double dec_wgs = (double)ceil_div((int64_t)d.b * d.g * S_d, waves / kWaves);
-    const double start = waves == 8 ? 4.3 : 3.4;
-    const double per_key = (waves == 8 ? 0.018 : 0.019) * (half ? 0.59 : 1.0);
+    const int64_t dec_wgs = ceil_div((int64_t)d.b * d.g * S_d, waves / kWaves);
+    const double start = waves == 8 ? 6.2 : 2.4;
+    const double per_key = (waves == 8 ? 0.0182 : 0.0175) * (half ? 0.62 : 1.0);
     const int64_t most = std::max<int64_t>(1, std::min(ceil_div(d.m_c, 128), 2 * slots / per_split));
     for (int64_t S = 1; S <= most; S += 1 + S / 8) {
       const int64_t keys = round_up(ceil_div(d.m_c, S), ck_step(64, d.m_c, S));
-      const double parts = (double)ceil_div(d.m_c, keys);
-      const double wgs = (double)per_split * parts;
-      const double busy = 1.0 + 0.15 * std::max(0.0, std::min(wgs, (double)kCUs) - 160.0) / 96.0;
+      const int64_t parts = ceil_div(d.m_c, keys);
+      const int64_t wgs = per_split * parts;
+      // the clock gives way as more than five eighths of the CUs run context
+      // work-groups; those that share a CU slow each other
+      const int64_t cus = std::min<int64_t>(wgs, kCUs);
+      const int64_t per_cu = ceil_div(std::min<int64_t>(wgs, slots), kCUs);
+      const double busy = (1.0 + 0.07 * (double)std::max<int64_t>(0, cus - 160) / 96.0) *
+                          (1.0 + 0.27 * (double)(per_cu - 1));
       const double tc = start + per_key * (double)keys * busy;
-      double t;
-      if (wgs >= slots) {
-        t = std::ceil(wgs / slots) * tc + dec_wgs * td / slots;
-      } else {
-        const double beside = std::ceil(dec_wgs / (slots - wgs)) * td;
-        t = std::max(tc, beside <= tc + td ? beside : (wgs * tc + dec_wgs * td) / slots + 0.5 * td);
-      }
-      const double loads = std::ceil(parts * d.d / 256) + std::ceil(4.0 * S_d * d.d / 256);
-      t = std::max(t, stream) + 0.15 * t + 2.4 * (std::ceil(loads / 16) - 1) +
-          (parts + 4 * S_d) * rows_all * (d.d * 4 + 16) / 2.2e6;
+      // whole rounds of context work-groups, then the last ones (if any) with
+      // the decode ones beside them
+      const int64_t rem = wgs % slots;
+      const double tr = rem ? tc : 0.0;
+      const double all_slots = (double)ceil_div(dec_wgs, slots - rem) * td;
+      const double beside = dec_wgs == 0           ? 0.0
+                            : all_slots <= tr + td ? all_slots
+                                                   : ((double)rem * tc + (double)dec_wgs * td) / slots + 0.5 * td;
+      double t = (double)(wgs / slots) * tc + std::max(tr, beside) + 0.05 * std::min(tr, beside);
+      const int64_t loads = ceil_div(parts * d.d, 256) + ceil_div(4 * S_d * d.d, 256);
+      t = std::max(t, stream) + 0.15 * t + 2.2 * (double)(ceil_div(loads, 16) - 1) +
+          (double)(parts + 4 * S_d) * rows_all * (d.d * 4 + 16) / 2.19e6;
       // of (nearly) equal ones the one with more splits: shorter work-groups
       const bool first = waves == 4 && S == 1;
       if (first || t < least * (waves == best.waves ? 1.005 : 1.0)) {
@@ -285,7 +295,13 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
     const int fork_env = coarse ? 0 : env_switch("BIFATTN_FORK");
     const int wide_env = env_switch("BIFATTN_CTX_WIDE");
     const bool both = d.d == 128;  // the 16x16 kernel is built for it
-    const bool one_launch = !coarse && P->dec_tiles <= 2 && !(both && wide_env == 0);
+    // Without decode rows there is no second launch for larger units either.
+    // The estimate serves them for many rows of d = 64, whose first split may
+    // pass the GPU (us per step: b 43, h 2048, g 32, m_c 919 85.4 -> 49.7; b 275,
+    // h 40, g 1, m_c 9142 73.0 -> 52.3); filling the GPU is the better rule for
+    // fewer rows and d = 128 (b 48, h 160, g 8, 2 tokens, m_c 2072 37.6, 41.8).
+    const bool estimated = P->dec_tiles <= 2 || (d.m_d_max == 0 && !both && M >= 1024);
+    const bool one_launch = !coarse && estimated && !(both && wide_env == 0);
     const bool big_decode = dec_bytes >= 16.0 * (1 << 20) && dec_bytes / 5e12 > 0.5 * ctx_flops / 1e15;
     P->fork = (allow_fork || one_launch) && d.m_d_max > 0 &&
               (fork_env == -1 ? one_launch || big_decode : fork_env == 1);

@@ -219,3 +219,18 @@ def test_four_query_tiles_leave_work_groups_for_the_decode_part(shape):
     with bif.Plan(*shape) as plan:
         info = plan.info()
         assert info["ctx_kernel"] == 0 and info["ctx_blocks"] <= 224
+
+
+@pytest.mark.gpu
+def test_many_row_splits_use_the_slots_there_are():
+    """Three four-wave work-groups of d = 64 fit a CU, two of d = 128; a last round
+    of few work-groups, or CUs of which some hold two and most one, are avoided."""
+    def blocks(*shape, **kw):
+        with bif.Plan(*shape, **kw) as plan:
+            info = plan.info()
+            print(f"[case] {shape} {info}", flush=True)
+            assert info["ctx_kernel"] == 2
+            return info["ctx_blocks"]
+    assert 384 < blocks(40, 40, 40, 64, 12000, 100) <= 768       # one row block: 320 -> 480 or so
+    assert blocks(27, 16, 8, 128, 35226, 0, n=2) <= 256           # was 296: 44.0 us, now 36.2
+    assert 512 < blocks(43, 2048, 32, 64, 919, 0, kv="int4") <= 768  # was two rounds of eight waves
