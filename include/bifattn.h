@@ -155,10 +155,10 @@ typedef enum {
  * device. On success *plan is set; on failure *plan is left NULL.
  * With dims.path = BIFATTN_PATH_AUTO the plan runs the standard path when
  * every (sample, group) unit fits in one round of work-groups on the GPU
- * (b*g <= 512), a unit has at most 32 query rows ((h/g)*n <= 32) and holds
- * few keys: m_c + m_d_max up to 500 to 1200 with d = 128 and 800 to 1800 with
- * d = 64, more with few units and many rows per group (b*(h/g)*n), and up to
- * 2200 with 481 to 512 units and 64 or more rows per group. There one launch
+ * (b*g <= 512), a unit has at most 32 query rows ((h/g)*n <= 32), it holds at
+ * most 3200 keys (m_c + m_d_max), and an estimate of both paths' times for
+ * these dimensions is lower for it: a few hundred keys for most layers, up to
+ * all 3200 where the query rows of all groups are many. There one launch
  * without partials beats reading the context once; otherwise the bifurcated
  * path. Both give the same attention (Appendix E.1).
  * Errors: EINVAL (null argument, b/h/g/m_c < 1, m_d_max < 0, n < 0,

@@ -152,6 +152,7 @@ int ck_step(int key_step, int64_t m_c, int64_t splits) {
 struct ManySplit {
   int waves = 4;
   int64_t splits = 1;
+  double us = 0.0;
 };
 ManySplit many_row_split(const bifattn_plan_s* P, int64_t rows) {
   const bifattn_dims_t& d = P->dims;
@@ -204,7 +205,35 @@ ManySplit many_row_split(const bifattn_plan_s* P, int64_t rows) {
       }
     }
   }
+  best.us = least;
   return best;
+}
+
+// Estimated times of a small step (at most 512 units of at most 32 query rows,
+// 3200 keys) on either path, us, from a fit to 6000 random layers timed on
+// both: within 16% and 20% of the time of 19 in 20.
+//   standard: a start (two query tiles 1.3 us more), then the keys, which take
+//     longer where two units share a CU and with two query tiles; the rows
+//     and the decode caches' bytes;
+//   bifurcated, few rows: start and combine, the context and the decode chunk,
+//     the partials, the work-groups.
+double standard_us(const bifattn_plan_s* P) {
+  const bifattn_dims_t& d = P->dims;
+  const bool half = d.d == 64, shared = (int64_t)d.b * d.g > kCUs, tiles2 = P->p > 16;
+  const double per_key = (half ? (shared ? 5.8 : 3.8) : (shared ? 11.0 : 7.3)) +
+                         (tiles2 ? (half ? 1.0 : 2.7) : 0.0);
+  return 4.8 + (tiles2 ? 1.3 : 0.0) + per_key * 1e-3 * ((double)d.m_c + d.m_d_max) +
+         2.4e-6 * (double)P->M * d.g * d.d +
+         0.031e-6 * 2.0 * d.b * d.g * (double)d.m_d_max * kv_row_bytes(d.d, d.kv_type);
+}
+double bifurcated_us(const bifattn_plan_s* P) {
+  const bifattn_dims_t& d = P->dims;
+  if (P->ctx_mode == kCtxLarge) return 4.5 + 1.17 * many_row_split(P, P->M).us;
+  const bool half = d.d == 64;
+  return 8.0 + (half ? 4.2e-3 : 7.0e-3) * ((double)d.m_c / P->S_c) +
+         (half ? 1.0e-3 : 4.0e-3) * std::min(P->dec_keys, d.m_d_max) +
+         1e-6 * (double)(P->S_c + 4 * P->S_d) * P->M * d.g * (d.d * 4 + 16) +
+         (half ? 0.3 : 1.1) / (2 * kCUs) * (double)(P->n_ctx_small_blocks + P->n_dec_blocks);
 }
 
 // Keys one replicated-ablation work-group reads: `start` by default, halved
@@ -347,24 +376,19 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
   // them into two launches.
   if (P->ctx_mode != kCtxLarge) P->fused = env_int("BIFATTN_LAUNCH", 1) == 1;
   // The workload-based switch: the standard path reads the context once per
-  // sample but needs one launch and no partials. It wins while every unit is
-  // resident in one round of work-groups (b*g <= 512), has at most two query
-  // tiles, and holds few keys: the crossovers measured over 24 layers at six
-  // context lengths each, by head dimension, units per CU (one, two) and rows
-  // per group (16, 32, 128, more): b 4, h = g = 8, d 128, 960 keys 13.3 us
-  // standard against 9.9; b 30, h 32, g 8, 1564 keys 18.1 against 14.3; b 60,
-  // h 32, g 4, 860 keys 12.3 against 15.3. (Units that fill the last sixteenth of the
-  // slots keep a line of 2200 keys from 64 rows per group, as callers have
-  // come to know it: 2112 keys there take about 30 us against 18.)
+  // sample but needs one launch and no partials. It is taken where its estimate
+  // is the lower one, while every unit is resident in one round of work-groups
+  // (b*g <= 512) and has at most two query tiles; past 3200 keys nothing was
+  // measured. Of those 6000 layers the choice is 0.4% slower than the faster
+  // path on average (11% at the 99th percentile); a line in keys by head dimension,
+  // units per CU and rows per group was 1.6% slower, since the rows of all groups
+  // and the decode rows matter as much (us per step, standard against bifurcated: b 64, h 32,
+  // g 8, 2164 keys 27.0, 17.3; b 256, h 32, g 2, 2164 keys 27.7, 33.9; b 18, h 32, g 8,
+  // 688 + 1024 keys 16.4, 21.6).
   if (d.path == BIFATTN_PATH_AUTO) {
-    static constexpr int kKeys[2][2][4] = {{{560, 900, 750, 1150}, {560, 600, 520, 1000}},
-                                           {{1200, 1500, 1450, 1800}, {800, 850, 830, 1200}}};
-    const int64_t keys = (int64_t)d.m_c + d.m_d_max;
-    const int64_t lmax = M >= 64 && units > 2 * kCUs * 15 / 16
-                             ? 2200
-                             : kKeys[d.d == 64][units > kCUs][M <= 16 ? 0 : M <= 32 ? 1 : M <= 128 ? 2 : 3];
-    const bool small = units <= 2 * kCUs && P->p <= 32 && keys <= lmax;
-    P->path = small ? BIFATTN_PATH_STANDARD : BIFATTN_PATH_BIFURCATED;
+    const bool small = units <= 2 * kCUs && P->p <= 32 && (int64_t)d.m_c + d.m_d_max <= 3200;
+    P->path = small && standard_us(P) <= bifurcated_us(P) ? BIFATTN_PATH_STANDARD
+                                                          : BIFATTN_PATH_BIFURCATED;
   } else {
     P->path = d.path;
   }
@@ -854,6 +878,7 @@ bifattn_status_t bifattn_decode_noalloc(const bifattn_dims_t* dims, const void* 
     if (st != BIFATTN_OK) return st;
     const WorkspaceLayout Lq = workspace_layout(&Q, false);
     if (Lq.bytes > kScratchBytes) return BIFATTN_ESCRATCH;
+    Q.path = P.path;
     P = Q;
     L = Lq;
   }

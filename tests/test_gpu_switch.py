@@ -89,8 +89,16 @@ def test_standard_path_poisoned_tail_and_flags():
     ((128, 32, 1, 128, 16384, 512), "bifurcated"),
     ((9, 64, 1, 128, 257, 33), "bifurcated"),   # 64 query rows per unit
     ((16, 32, 32, 128, 1024, 64), "bifurcated"),  # 512 units of 1088 keys
-    ((64, 32, 8, 128, 2048, 64), "standard"),   # 256 rows per group
     ((4, 32, 8, 128, 2048, 64), "bifurcated"),  # 16 rows per group
+    # measured on both paths, us per step (standard, bifurcated)
+    ((64, 32, 8, 128, 2048, 64), "bifurcated"),   # 26, 17: 512 units of 2112 keys,
+    ((60, 32, 8, 128, 2048, 64), "bifurcated"),   # 26, 17: as with 480 units
+    ((256, 32, 2, 128, 1700, 64), "standard"),    # 24, 30: 8192 rows
+    ((512, 8, 1, 128, 1000, 64), "standard"),     # 17, 23
+    ((18, 32, 8, 128, 688, 1024), "standard"),    # 16, 22: more decode than context rows
+    ((12, 160, 40, 64, 1464, 64, 0.0, 4, "int4"), "standard"),  # 14, 25
+    ((4, 8, 8, 128, 960, 64), "bifurcated"),      # 13, 10
+    ((32, 32, 16, 64, 2000, 64), "bifurcated"),   # 17, 11
 ])
 def test_automatic_choice(shape, expect):
     with bif.Plan(*shape) as plan:
