@@ -7,8 +7,9 @@ dtype, device and contiguity before their device pointers are handed over,
 so a mismatched tensor is refused on the host instead of being read out of
 bounds on the GPU. The per-step calls (decode, append) first go through the
 same checks in native code (``_bifattn_bind.so``), which leaves every call it
-does not take to the checks here. There is no fallback: without the built
-libraries every entry point raises.
+does not take to the checks here; where it is missing or built for another
+torch, the checks here take them all, with a warning. There is no fallback for
+the kernels: without libbifattn.so every entry point raises.
 """
 from __future__ import annotations
 
@@ -16,6 +17,7 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libbifattn.so")
@@ -105,34 +107,54 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
-_bind = None
+_bind = None  # the module once loaded, False where it cannot be used
 
 
 def _bind_module():
-    """The native argument checks (_bifattn_bind.so, built in-tree)."""
+    """The native argument checks (_bifattn_bind.so, built in-tree), or None
+    where they are missing or built against another torch (warned of once)."""
     global _bind
     if _bind is None:
-        if not os.path.exists(BIND_PATH):
-            raise RuntimeError(f"{BIND_PATH} is missing: build it with "
-                               "`python -m paper_2403_08845_amd.build`")
-        import torch  # noqa: F401  (its libraries are the module's)
-        loader = importlib.machinery.ExtensionFileLoader("_bifattn_bind", BIND_PATH)
-        mod = importlib.util.module_from_spec(importlib.util.spec_from_loader("_bifattn_bind", loader))
-        loader.exec_module(mod)
-        _bind = mod
-    return _bind
+        import torch  # its libraries are the module's
+        why = "missing"
+        _bind = False
+        if os.path.exists(BIND_PATH):
+            loader = importlib.machinery.ExtensionFileLoader("_bifattn_bind", BIND_PATH)
+            spec = importlib.util.spec_from_loader("_bifattn_bind", loader)
+            try:
+                mod = importlib.util.module_from_spec(spec)
+                loader.exec_module(mod)
+                if mod.torch_version == torch.__version__.partition("+")[0]:
+                    _bind = mod
+                else:
+                    why = f"built for torch {mod.torch_version}, this is {torch.__version__}"
+            except ImportError as e:
+                why = str(e)
+        if not _bind:
+            warnings.warn(f"{BIND_PATH}: {why}; the per-step calls check their arguments in Python "
+                          "(several us a call). Build it with `python -m paper_2403_08845_amd.build`",
+                          RuntimeWarning, stacklevel=2)
+    return _bind or None
+
+
+def _raw_stream_getter():
+    """A callable: device index -> torch's current stream there, as an int."""
+    torch = _torch()
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return raw or (lambda index: torch.cuda.current_stream(index).cuda_stream)
 
 
 def _caller(dims, handle, device_index):
-    """The native caller of a plan's per-step entry points."""
-    import torch
+    """The native caller of a plan's per-step entry points, or None."""
+    bind = _bind_module()
+    if bind is None:
+        return None
     L = lib()
     addr = [ctypes.cast(f, ctypes.c_void_p).value
             for f in (L.bifattn_decode_scaled, L.bifattn_append_kv)]
     D = dims
-    return _bind_module().Caller(*addr, handle.value, torch._C._cuda_getCurrentRawStream,
-                                 device_index, D.b, D.h, D.g, D.d, D.m_c, D.m_d_max, max(1, D.n),
-                                 D.kv_type)
+    return bind.Caller(*addr, handle.value, _raw_stream_getter(), device_index, D.b, D.h, D.g, D.d,
+                       D.m_c, D.m_d_max, max(1, D.n), D.kv_type)
 
 
 def status_string(status: int) -> str:
@@ -216,12 +238,8 @@ def _stream_ptr(stream, device=None):
     """A torch stream, a raw hipStream_t (int), or None for torch's current
     stream of `device`."""
     if stream is None:
-        torch = _torch()
-        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        if raw is not None:
-            return ctypes.c_void_p(raw(device.index if device is not None
-                                       else torch.cuda.current_device()))
-        stream = torch.cuda.current_stream(device)
+        return ctypes.c_void_p(_raw_stream_getter()(
+            device.index if device is not None else _torch().cuda.current_device()))
     return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
 

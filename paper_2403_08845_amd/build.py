@@ -6,11 +6,13 @@ binding's native part with the host compiler.
 Compiles the HIP kernels and the host-side C ABI into
 ``paper_2403_08845_amd/libbifattn.so``. Packed fp32 VALU instructions are
 disabled for all device code. ``_bifattn_bind.so`` beside it (host code only,
-against torch's headers) checks the arguments of the per-step calls.
+against torch's headers) checks the arguments of the per-step calls; without
+a host compiler or those headers it is left out, and Python checks them.
 """
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -54,13 +56,33 @@ def _run(cmd, verbose: bool) -> None:
         print(err, file=sys.stderr)
 
 
+def _cxx() -> str:
+    return os.environ.get("CXX", "g++")
+
+
+def bind_obstacle() -> str | None:
+    """What keeps the binding's native part from being built here, if anything."""
+    if shutil.which(_cxx()) is None:
+        return f"no host compiler ({_cxx()})"
+    try:
+        from torch.utils.cpp_extension import include_paths
+    except ImportError as e:
+        return f"torch is not importable ({e})"
+    headers = {os.path.join("torch", "csrc", "autograd", "python_variable.h"): include_paths(),
+               "Python.h": [sysconfig.get_paths()["include"]]}
+    for name, dirs in headers.items():
+        if not any(os.path.exists(os.path.join(d, name)) for d in dirs):
+            return f"{name} not found"
+    return None
+
+
 def build_bind(verbose: bool = False) -> str:
     import torch
     from torch.utils.cpp_extension import include_paths, library_paths
     tmp = BIND + ".tmp"
-    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc())))
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(shutil.which(hipcc()) or hipcc())))
     dirs = [INCLUDE, os.path.join(rocm, "include"), sysconfig.get_paths()["include"], *include_paths()]
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+    cmd = [_cxx(), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
            "-D__HIP_PLATFORM_AMD__", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            *[f"-I{d}" for d in dirs], BIND_SRC, "-o", tmp,
            *[f"-L{d}" for d in library_paths()], "-ltorch_python", "-ltorch_cpu", "-lc10"]
@@ -73,7 +95,11 @@ def build(verbose: bool = False) -> str:
     tmp = LIB + ".tmp"
     _run([hipcc(), *HIPCC_FLAGS, *SOURCES, "-o", tmp], verbose)
     os.replace(tmp, LIB)
-    build_bind(verbose)
+    why = bind_obstacle()
+    if why is None:
+        build_bind(verbose)
+    else:
+        print(f"{os.path.basename(BIND)} not built: {why}", file=sys.stderr)
     return LIB
 
 

@@ -13,6 +13,7 @@
 // raise the specific error or make the call themselves, so what is accepted
 // and what is refused does not depend on this file.
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include <cstdint>
 
@@ -231,6 +232,11 @@ PyMODINIT_FUNC PyInit__bifattn_bind() {
   Py_INCREF(&caller_type);
   if (PyModule_AddObject(m, "Caller", reinterpret_cast<PyObject*>(&caller_type)) < 0) {
     Py_DECREF(&caller_type);
+    Py_DECREF(m);
+    return nullptr;
+  }
+  // The tensor layouts read above are this version's.
+  if (PyModule_AddStringConstant(m, "torch_version", TORCH_VERSION) < 0) {
     Py_DECREF(m);
     return nullptr;
   }

@@ -1,6 +1,7 @@
 """The native argument checks of the per-step calls against the Python
 checks: the same calls are taken, the same ones refused with the same error."""
 import ctypes
+import warnings
 
 import pytest
 
@@ -23,6 +24,49 @@ def test_host_tensors_are_left_to_the_python_checks():
     assert c.append(kd, kd, kd, kd, lens, 0) is None
     with pytest.raises(TypeError):
         c.decode(q, kc)
+
+
+@pytest.mark.parametrize("obstacle", ["missing", "other torch", "unloadable"])
+def test_without_the_native_checks_python_takes_every_call(obstacle, monkeypatch, tmp_path):
+    torch = pytest.importorskip("torch")
+    monkeypatch.setattr(bif, "_bind", None)
+    if obstacle == "missing":
+        monkeypatch.setattr(bif, "BIND_PATH", str(tmp_path / "none.so"))
+    elif obstacle == "unloadable":
+        (tmp_path / "bad.so").write_bytes(b"no library")
+        monkeypatch.setattr(bif, "BIND_PATH", str(tmp_path / "bad.so"))
+    else:
+        monkeypatch.setattr(torch, "__version__", "1.13.0+other")
+    dims = bif.Dims(B, H, G, D, MC, MD, 0.0)
+    with pytest.warns(RuntimeWarning, match="check their arguments in Python"):
+        assert bif._caller(dims, ctypes.c_void_p(16), 0) is None
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")  # once is enough
+        assert bif._caller(dims, ctypes.c_void_p(16), 0) is None
+
+
+def test_current_stream_without_the_raw_getter(monkeypatch):
+    torch = pytest.importorskip("torch")
+
+    class Stream:
+        cuda_stream = 7
+
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: Stream)
+    assert bif._raw_stream_getter()(0) == 7
+    assert bif._stream_ptr(None, torch.device("cuda", 0)).value == 7
+    assert bif._caller(bif.Dims(B, H, G, D, MC, MD, 0.0), ctypes.c_void_p(16), 0) is not None
+
+
+def test_the_library_is_built_without_a_host_compiler(monkeypatch, capsys):
+    from paper_2403_08845_amd import build
+    ran = []
+    monkeypatch.setenv("CXX", "/no/such/compiler")
+    monkeypatch.setattr(build, "_run", lambda cmd, verbose: ran.append(cmd[0]))
+    monkeypatch.setattr(build.os, "replace", lambda a, b: ran.append(b))
+    assert build.build() == build.LIB
+    assert ran == [build.hipcc(), build.LIB]
+    assert "no host compiler" in capsys.readouterr().err
 
 
 def _args(torch, kv, n):
@@ -84,6 +128,7 @@ def test_native_and_python_checks_agree(kv, n):
     torch.manual_seed(0)
     with bif.Plan(B, H, G, D, MC, MD, n=n, kv=kv) as plan:
         native = plan._caller
+        assert native is not None  # the module that was built loads
         a = _args(torch, kv, n)
         for name, x in _forms(torch, a, kv, n):
             print(f"[case] {kv} n={n} {name}", flush=True)
