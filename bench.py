@@ -71,7 +71,7 @@ def kernel_source_hash() -> str:
 
 def measured_traffic(workload: str, kernel: str = "partials"):
     """HBM bytes per launch of a kernel ("partials": the partial launch;
-    "ctx_large": the many-row context kernel) from the committed rocprofv3
+    "ctx_wide": the many-row context kernel's) from the committed rocprofv3
     counter summary, or None when it is missing or the kernel source changed
     since the counters were taken."""
     path = os.path.join(TRAFFIC_DIR, f"traffic_{kernel}_{workload}.json")
@@ -164,15 +164,15 @@ def calibrate_copy(reps: int = 5):
     log(f"[bench] copy-equivalent kernel over {COPY_BYTES} bytes, {reps} times")
 
 
-KERNEL_NAMES = {"partials": "partials_kernel", "ctx_large": "ctx_large_kernel",
-                "ctx_wide": "ctx_wide_kernel", "standard": "standard_kernel"}
+KERNEL_NAMES = {"partials": "partials_kernel", "ctx_wide": "ctx_wide_kernel",
+                "standard": "standard_kernel"}
 
 
 def summarize_profile(stats_dir: str, fetch_dir: str, write_dir: str, workload: str, out_dir: str,
                       warmup: int, steps: int, kernel: str = "partials"):
     """Turn rocprofv3 outputs into the committed summary: the kernel-trace
     statistics, and one kernel's HBM traffic per launch ("partials": the
-    partial launch, "ctx_large": the many-row context kernel) from the two
+    partial launch, "ctx_wide": the many-row context kernel's) from the two
     counter runs, each scaled by what the same counter reads for the plain
     copy of COPY_BYTES."""
     kname = KERNEL_NAMES[kernel]
@@ -264,17 +264,17 @@ def summarize_profile(stats_dir: str, fetch_dir: str, write_dir: str, workload: 
 
 def algorithmic_read_bytes(workload: str, kernel: str):
     """(description, bytes) of the KV a kernel must read once for the
-    workload: the context chunk of every group for the many-row 16x16 context
-    kernel, the context and the valid decode rows for the launches that hold
-    both (the few-row partial launch, the 32x32 kernel's over units of at most
-    32 query rows); None for unknown workloads."""
+    workload: the context and the valid decode rows for the launches that hold
+    both parts (the few-row partial launch, the many-row context kernel's over
+    units of at most 32 query rows), else those of the part; None for unknown
+    workloads."""
     w = workloads.WORKLOADS.get(workload)
     if w is None:
         return None
     rb = workloads.row_bytes(w.d, w.kv)
     ctx = 2 * rb * w.g * w.m_c
     rows = w.h // w.g * w.n
-    if kernel == "ctx_large" or (kernel == "ctx_wide" and rows > 32):
+    if kernel == "ctx_wide" and rows > 32:
         return "one copy of the context K and V", ctx
     lens = workloads.make_workload_lens(w)
     dec = 2 * rb * w.g * int(np.sum(lens, dtype=np.int64))
@@ -490,11 +490,10 @@ def main():
         # The many-row context kernel: a contraction over b*p*n rows per group.
         launch_flops = flops if one_launch else ctx_flops
         tflops = launch_flops / (ctx_us * 1e-6) / 1e12
-        ck = "ctx_wide" if info.get("ctx_kernel") == 2 else "ctx_large"
-        roofline = {"kernel": f"{KERNEL_NAMES[ck]} (many-row context partials)", "bound": "mfma",
+        roofline = {"kernel": "ctx_wide_kernel (many-row context partials)", "bound": "mfma",
                     "achieved": round(tflops, 1), "peak": MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(tflops / MFMA_PEAK_TFLOPS, 4),
-                    "traffic": measured_traffic(w.name, ck),
+                    "traffic": measured_traffic(w.name, "ctx_wide"),
                     "avg_launch_us": round(ctx_us, 3), "flops_per_launch": launch_flops,
                     "bytes_per_launch": B_kv if one_launch else ctx_bytes}
     elif many_rows:

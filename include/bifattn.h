@@ -136,8 +136,8 @@ typedef struct {
                                  BIFATTN_PATH_STANDARD */
   size_t workspace_bytes;     /* device memory the plan owns */
   int32_t ctx_kernel;         /* context work-groups: 0 in the partial launch (few rows per
-                                 group, or none), 1 many-row kernel of 16-row waves, 2 many-row
-                                 32x32 MFMA kernel of 32-row waves */
+                                 group, or none), 2 many-row 32x32 MFMA kernel of 32-row waves
+                                 (1 is not used) */
   int32_t side_stream;        /* 1 when the decode launch runs on the plan's side stream */
 } bifattn_plan_info_t;
 
@@ -191,7 +191,7 @@ bifattn_status_t bifattn_plan_get_info(bifattn_plan_t plan, bifattn_plan_info_t 
  * which merges the (max, sum, weighted-value) partials of both parts into
  * `out`. (a) and (b) are one launch, except with many query rows per group
  * (b*(h/g)*n > 32) where (h/g)*n > 32: there (b) follows (a), or,
- * with a large decode cache, runs on a stream the plan owns, beside (a), and
+ * with a large decode cache and at least 128 rows per group, runs on a stream the plan owns, beside (a), and
  * `stream` waits for it before (c). On a plan whose path is BIFATTN_PATH_STANDARD it enqueues one
  * launch instead: per (sample, group), the context rows then the decode
  * rows in one softmax, written to `out`. Kd, Vd and decode_lens may be NULL only when m_d_max == 0.

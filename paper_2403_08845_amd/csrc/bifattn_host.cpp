@@ -23,7 +23,7 @@ struct bifattn_plan_s {
   int ctx_mode = kCtxNone;
   int dec_tiles = 1;
   int ctx_keys = 0, S_c = 0, ctx_row_blocks = 1, n_ctx_blocks = 0, n_ctx_small_blocks = 0;
-  int ctx_wide = 0;  // many-row path: waves per work-group of the 32x32 kernel, or 0
+  int ctx_wide = 0;  // many-row path: waves per work-group of its context kernel (8 or 4)
   int dec_keys = 0, S_d = 0, n_dec_blocks = 0;
   int rep_keys = 0, S_r = 0, n_rep_blocks = 0;
   int fused = 1;       // context and decode work-groups in one launch
@@ -123,12 +123,10 @@ int dec_chunk_keys(int64_t units, int64_t rows, int least) {
   while (keys / 2 >= least && units * ceil_div(rows, keys) < kCUs / 2) keys /= 2;
   return keys;
 }
-// Rounding of the many-row context chunk: the wide kernel runs 128-key
-// stages when its chunks are multiples of 128 keys, so chunks of at least
-// 1024 keys are rounded to 128.
-int ck_step(int key_step, int64_t m_c, int64_t splits) {
-  return key_step == 64 && ceil_div(m_c, splits) >= 1024 ? 128 : key_step;
-}
+// Rounding of the many-row context chunk: its kernel runs 128-key stages when
+// its chunks are multiples of 128 keys, so chunks of at least 1024 keys are
+// rounded to 128, shorter ones to the 64 keys of its smaller stages.
+int ck_step(int64_t m_c, int64_t splits) { return ceil_div(m_c, splits) >= 1024 ? 128 : 64; }
 
 // Waves per work-group and key splits of a launch that holds the 32x32
 // context work-groups and the decode work-groups. More splits shorten the
@@ -174,7 +172,7 @@ ManySplit many_row_split(const bifattn_plan_s* P, int64_t rows) {
     const double per_key = (waves == 8 ? 0.0182 : 0.0175) * (half ? 0.62 : 1.0);
     const int64_t most = std::max<int64_t>(1, std::min(ceil_div(d.m_c, 128), 2 * slots / per_split));
     for (int64_t S = 1; S <= most; S += 1 + S / 8) {
-      const int64_t keys = round_up(ceil_div(d.m_c, S), ck_step(64, d.m_c, S));
+      const int64_t keys = round_up(ceil_div(d.m_c, S), ck_step(d.m_c, S));
       const int64_t parts = ceil_div(d.m_c, keys);
       const int64_t wgs = per_split * parts;
       // the clock gives way as more than five eighths of the CUs run context
@@ -304,8 +302,7 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
     P->ctx_row_blocks = 1;
   } else {
     // Many rows take the 32x32 MFMA kernel (work-groups of eight or four
-    // waves of 32 rows); d = 128 has the kernel of 16-row waves too (eight per
-    // work-group, two work-groups per CU), which BIFATTN_CTX_WIDE=0 forces.
+    // waves of 32 rows).
     //
     // The context part is bound by the matrix cores and the decode part by
     // HBM, so they run beside each other. The 32x32 kernel's launch holds the
@@ -315,27 +312,27 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
     // samples over 16k, 64.2 -> 53.7-57; 4 draft tokens 89-95 -> 81.6; b 40,
     // h 32, g 8, m_c 3000 31.6 -> 19.5. Otherwise a large decode part (16 MiB
     // or more, its HBM time at ~5 TB/s above half the context's matrix time
-    // at ~1 PFLOP/s) goes to the plan's side stream, and a small one follows
-    // the context kernel. BIFATTN_FORK=0/1 forces the parts behind or beside
-    // each other.
+    // at ~1 PFLOP/s) goes to the plan's side stream from 128 rows per group;
+    // a small one, or one beside fewer rows, follows the context kernel (44
+    // layers of 66 to 126 rows and large decode parts take 8% less time so
+    // than on the side stream, whose fork and join are about 10 us of their
+    // 40 to 100; waves of 16 rows for the context there took 1% more).
+    // BIFATTN_FORK=0/1 forces the parts behind or beside each other.
     P->ctx_mode = kCtxLarge;
     const double dec_bytes = 2.0 * d.b * d.g * (double)d.m_d_max * kv_row_bytes(d.d, d.kv_type);
     const double ctx_flops = 4.0 * d.h * P->ntok * d.d * (double)d.b * d.m_c;
     const int fork_env = coarse ? 0 : env_switch("BIFATTN_FORK");
-    const int wide_env = env_switch("BIFATTN_CTX_WIDE");
-    const bool both = d.d == 128;  // the 16x16 kernel is built for it
     // Without decode rows there is no second launch for larger units either.
     // The estimate serves them for many rows of d = 64, whose first split may
     // pass the GPU (us per step: b 43, h 2048, g 32, m_c 919 85.4 -> 49.7; b 275,
     // h 40, g 1, m_c 9142 73.0 -> 52.3); filling the GPU is the better rule for
     // fewer rows and d = 128 (b 48, h 160, g 8, 2 tokens, m_c 2072 37.6, 41.8).
-    const bool estimated = P->dec_tiles <= 2 || (d.m_d_max == 0 && !both && M >= 1024);
-    const bool one_launch = !coarse && estimated && !(both && wide_env == 0);
+    const bool estimated = P->dec_tiles <= 2 || (d.m_d_max == 0 && d.d == 64 && M >= 1024);
+    const bool one_launch = !coarse && estimated;
     const bool big_decode = dec_bytes >= 16.0 * (1 << 20) && dec_bytes / 5e12 > 0.5 * ctx_flops / 1e15;
     P->fork = (allow_fork || one_launch) && d.m_d_max > 0 &&
-              (fork_env == -1 ? one_launch || big_decode : fork_env == 1);
+              (fork_env == -1 ? one_launch || (big_decode && M >= 128) : fork_env == 1);
     P->fused = one_launch && P->fork;
-    const bool wide = !both || (wide_env == -1 ? one_launch || !P->fork || M >= 128 : wide_env == 1);
     const int wgs = env_int("BIFATTN_CTX_WGS", 0);
     ManySplit split;
     if (one_launch && wgs == 0) {
@@ -343,24 +340,22 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
     } else {
       split.waves = M >= 256 ? 8 : 4;
     }
-    P->ctx_wide = wide ? split.waves : 0;
-    const int block_rows = wide ? 32 * P->ctx_wide : kLargeRowsPerBlock;
-    P->ctx_row_blocks = (int)ceil_div(M, block_rows);
-    const int key_step = wide ? 64 : kTileKeys;  // keys per stage of the kernel's loop
+    P->ctx_wide = split.waves;
+    P->ctx_row_blocks = (int)ceil_div(M, 32 * P->ctx_wide);
     if (!one_launch || wgs > 0) {
       // With the decode work-groups in a launch of their own: about one
       // work-group per CU for eight-wave work-groups, two for four-wave ones;
       // beside the side stream, one per CU (five eighths of that with eight
-      // waves of 32 rows: the decode work-groups take the rest).
+      // waves: the decode work-groups take the rest).
       const int target = P->fork ? (P->ctx_wide == 8 ? kCUs * 5 / 8 : kCUs)
                                  : (P->ctx_wide == 8 ? kCUs : 2 * kCUs);
       split.splits = ceil_div(wgs > 0 ? wgs : target, (int64_t)d.g * P->ctx_row_blocks);
     }
-    if (coarse && !both) split.splits = ceil_div(2 * kCUs, d.g * ceil_div(M, kLargeRowsPerBlock));
+    if (coarse && d.d == 64) split.splits = ceil_div(2 * kCUs, d.g * ceil_div(M, 128));
     const int64_t splits = std::max<int64_t>(1, split.splits);
-    int64_t ck = round_up(ceil_div(d.m_c, splits), ck_step(key_step, d.m_c, splits));
+    int64_t ck = round_up(ceil_div(d.m_c, splits), ck_step(d.m_c, splits));
     if (coarse && M <= 64) ck = long_keys;
-    P->ctx_keys = (int)round_up(env_int("BIFATTN_CTX_KEYS", (int)ck), key_step);
+    P->ctx_keys = (int)round_up(env_int("BIFATTN_CTX_KEYS", (int)ck), 64);
   }
   P->S_c = (int)ceil_div(d.m_c, P->ctx_keys);
   P->n_ctx_blocks = P->ctx_mode == kCtxLarge ? d.g * P->S_c * P->ctx_row_blocks : 0;
@@ -717,7 +712,7 @@ bifattn_status_t bifattn_plan_get_info(bifattn_plan_t P, bifattn_plan_info_t* in
   info->fused = P->fused;
   info->path = P->path;
   info->workspace_bytes = P->ws_bytes;
-  info->ctx_kernel = P->ctx_mode != kCtxLarge ? 0 : (P->ctx_wide ? 2 : 1);
+  info->ctx_kernel = P->ctx_mode != kCtxLarge ? 0 : 2;
   info->side_stream = P->fork && !P->fused;
   return BIFATTN_OK;
 }

@@ -15,11 +15,6 @@ constexpr int kThreads = 64 * kWaves;
 constexpr int kTileKeys = 32;
 // Query rows per MFMA N-tile.
 constexpr int kRowsPerTile = 16;
-// Context path with many query rows per group: work-groups of eight waves,
-// one 16-row query tile each.
-constexpr int kLargeWaves = 8;
-constexpr int kLargeThreads = 64 * kLargeWaves;
-constexpr int kLargeRowsPerBlock = kLargeWaves * kRowsPerTile;  // 128
 // Largest group size the per-sample decode path holds in registers.
 constexpr int kMaxP = 64;
 // Lazy softmax rescaling: the running reference maximum is only raised when a
@@ -66,8 +61,7 @@ struct PartialsParams {
   int ctx_keys;           // keys per context work-group (many-row path)
   int S_c;
   int ctx_row_blocks;
-  int ctx_wide;           // many-row path: waves of 32 rows per work-group (32x32 MFMA
-                          // kernel), or 0 for the kernel of eight 16-row waves
+  int ctx_wide;           // many-row path: waves of 32 rows per work-group (8 or 4)
   int dec_keys;           // keys per decode work-group
   int S_d;
   int n_ctx_blocks;       // work-groups of the many-row context path
@@ -149,8 +143,8 @@ constexpr size_t kScratchBytes = size_t(64) << 20;
 // that device current; later calls return the cached address).
 hipError_t scratch_address(int device, void** ptr);
 
-// Launch the many-row context kernel over n_ctx_blocks work-groups; the 32x32
-// kernel's launch also holds the n_dec_blocks decode work-groups (dec_tiles
+// Launch the many-row context kernel over n_ctx_blocks work-groups; the
+// launch also holds the n_dec_blocks decode work-groups (dec_tiles
 // query tiles, at most 2).
 hipError_t launch_ctx_large(const PartialsParams& P, int d, int kv, int dec_tiles,
                             hipStream_t stream, const LaunchEvents& ev = {});

@@ -172,16 +172,6 @@ template <> struct Raw<2> {
   static __device__ __forceinline__ type zero() { return 0u; }
   static __device__ __forceinline__ uint32_t word(const type& v, int) { return v; }
 };
-template <> struct Raw<1> {
-  typedef uint32_t type;
-  template <int AUX = 0>
-  static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t r, int off) {
-    return __builtin_amdgcn_raw_buffer_load_b8(r, off, 0, AUX);
-  }
-  static __device__ __forceinline__ type zero() { return 0u; }
-  static __device__ __forceinline__ uint32_t word(const type& v, int) { return v; }
-};
-
 // Pack element t of two bf16 value rows (even key, odd key) into one word.
 __device__ __forceinline__ uint32_t pair_elem(uint32_t even_w, uint32_t odd_w, int t) {
   return (t & 1) ? ((even_w >> 16) | (odd_w & 0xffff0000u))
@@ -306,33 +296,25 @@ __device__ __forceinline__ u32x4 load16(const uint16_t* p) {
 // same order, as the V^T operand a lane builds from value rows 4e + G.
 __device__ __forceinline__ int qk_key(int a, int r) { return 16 * a + 4 * (r & 3) + (r >> 2); }
 
-// Per-wave running state of NT query tiles. With MS (matrix-core sums) the
-// row sums come from one more MFMA per tile against an all-ones operand:
-// lacc holds the row's sum of the bf16-rounded weights (the weights the
-// values are multiplied by) in all four of its elements, instead of the
-// lane's share of the fp32 weights in l.
-// With OFF (int4 caches of the streaming waves, see kInt4Offset) the operands
+// Per-wave running state of NT query tiles. With OFF (int4 caches of the streaming waves, see kInt4Offset) the operands
 // hold each code's value plus an offset: bias starts every logit at minus the
-// offset's share, and lacc's sums of the rounded weights take it out of acc
-// at the end and every kOffsetTiles tiles (take_offset).
-template <int D, int NT, bool MS = false, bool OFF = false> struct RowState {
+// offset's share, and lacc's sums of the rounded weights (one more MFMA per
+// tile against an all-ones operand) take it out of acc at the end and every kOffsetTiles tiles (take_offset).
+template <int D, int NT, bool OFF = false> struct RowState {
   static constexpr int DV = D / 16;
-  static constexpr bool kSums = MS || OFF;  // sums of the rounded weights by the matrix cores
   float mref[NT];       // reference maximum (log2 units), uniform over the row's 4 lanes
-  float nbase[MS ? NT : 1];  // with MS: -mref, or 0 while mref = -inf (the exponent's offset)
   float thr[NT];        // raw-logit threshold: a logit above it calls for a higher mref
-  float l[NT];          // this lane's share of the row sum (without MS)
-  f32x4 lacc[kSums ? NT : 1];  // sums of the rounded weights (with MS or OFF)
-  f32x4 bias[OFF ? NT : 1];    // first accumulator of the logits (with OFF)
+  float l[NT];          // this lane's share of the row sum
+  f32x4 lacc[OFF ? NT : 1];  // sums of the rounded weights (with OFF), in all four elements
+  f32x4 bias[OFF ? NT : 1];  // first accumulator of the logits (with OFF)
   f32x4 acc[NT][DV];    // O^T accumulators
   __device__ __forceinline__ void init() {
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       mref[nt] = kNegInf;
-      if constexpr (MS) nbase[nt] = 0.f;
       thr[nt] = kNegInf;
       l[nt] = 0.f;
-      if constexpr (kSums) lacc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (OFF) lacc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int t = 0; t < DV; ++t) acc[nt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
@@ -350,8 +332,8 @@ template <int D, int NT, bool MS = false, bool OFF = false> struct RowState {
 // (ntok = 1 masks keys >= rem). Keys below `vfloor` (counted from the tile's
 // first key, like rem) are seen by every row whatever its causal limit: the
 // context rows that precede the decode rows in a replicated cache.
-template <int D, int NT, bool MS, bool OFF, typename KOp, typename VOp, typename QOp>
-__device__ __forceinline__ void tile_update(RowState<D, NT, MS, OFF>& st, KOp&& k_at, VOp&& vop_at,
+template <int D, int NT, bool OFF, typename KOp, typename VOp, typename QOp>
+__device__ __forceinline__ void tile_update(RowState<D, NT, OFF>& st, KOp&& k_at, VOp&& vop_at,
                                             QOp&& q_at, int rem, int ntok, int vfloor,
                                             float scale_log2, int lane) {
   constexpr int KS = D / 32;
@@ -365,7 +347,6 @@ __device__ __forceinline__ void tile_update(RowState<D, NT, MS, OFF>& st, KOp&& 
     else
       sacc[nt][0] = sacc[nt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  if constexpr (MS) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
   for (int s = 0; s < KS; ++s) {
     const u32x4 k0 = k_at(0, s), k1 = k_at(1, s);
@@ -376,7 +357,6 @@ __device__ __forceinline__ void tile_update(RowState<D, NT, MS, OFF>& st, KOp&& 
       sacc[nt][1] = mfma_bf16(k1, qo, sacc[nt][1]);
     }
   }
-  if constexpr (MS) __builtin_amdgcn_s_setprio(0);
   // Raw logits; scale_log2 > 0, so maxima can be taken before scaling and
   // the scale folds into the exponent's multiply-add. The reference maximum
   // only has to bound the row's logits to within 2^kRescaleSlack (the same
@@ -417,35 +397,28 @@ __device__ __forceinline__ void tile_update(RowState<D, NT, MS, OFF>& st, KOp&& 
       // Rows that do not raise keep alpha = 1 (and never form -inf - -inf).
       const bool raise = tmax > st.mref[nt] + kRescaleSlack;
       const float alpha = raise ? exp2_fast(st.mref[nt] - tmax) : 1.f;  // 0 when mref = -inf
-      if constexpr (MS || OFF) st.lacc[nt] *= alpha;
-      if constexpr (!MS) st.l[nt] *= alpha;
+      if constexpr (OFF) st.lacc[nt] *= alpha;
+      st.l[nt] *= alpha;
 #pragma unroll
       for (int t = 0; t < DV; ++t) st.acc[nt][t] *= alpha;
       st.mref[nt] = raise ? tmax : st.mref[nt];
-      if constexpr (MS) st.nbase[nt] = st.mref[nt] == kNegInf ? 0.f : -st.mref[nt];
       st.thr[nt] = (st.mref[nt] + kRescaleSlack) / scale_log2;
     }
   }
   auto weights = [&](int nt) -> u32x4 {  // bf16 P^T operand of query tile nt; adds to the sums
-    // kept in the state with MS; recomputed per tile otherwise (registers)
-    float nbase;
-    if constexpr (MS)
-      nbase = st.nbase[nt];
-    else
-      nbase = st.mref[nt] == kNegInf ? 0.f : -st.mref[nt];
+    // recomputed per tile (registers)
+    const float nbase = st.mref[nt] == kNegInf ? 0.f : -st.mref[nt];
     float pr[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) pr[e] = exp2_fast(__builtin_fmaf(x[nt][e], scale_log2, nbase));
-    if constexpr (!MS) {
-      float psum = pr[0];
+    float psum = pr[0];
 #pragma unroll
-      for (int e = 1; e < 8; ++e) psum += pr[e];
-      st.l[nt] += psum;
-    }
+    for (int e = 1; e < 8; ++e) psum += pr[e];
+    st.l[nt] += psum;
     u32x4 pb;
 #pragma unroll
     for (int w = 0; w < 4; ++w) pb[w] = pack_bf16(pr[2 * w], pr[2 * w + 1]);
-    if constexpr (MS || OFF) {
+    if constexpr (OFF) {
       constexpr uint32_t kOnes = 0x3F803F80u;  // two bf16 1.0
       st.lacc[nt] = mfma_bf16(u32x4{kOnes, kOnes, kOnes, kOnes}, pb, st.lacc[nt]);
     }
@@ -474,10 +447,8 @@ __device__ __forceinline__ void tile_update(RowState<D, NT, MS, OFF>& st, KOp&& 
     for (int t = 0; t < DV; ++t) st.acc[1][t] = mfma_bf16(vo[t], pb1, st.acc[1][t]);
   } else if constexpr (NT == 1) {
     const u32x4 pb = weights(0);
-    if constexpr (MS) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int t = 0; t < DV; ++t) st.acc[0][t] = mfma_bf16(vop_at(t), pb, st.acc[0][t]);
-    if constexpr (MS) __builtin_amdgcn_s_setprio(0);
   } else {
     // Many query tiles: registers are short, so each V^T operand is formed
     // once and used for every tile.
@@ -625,7 +596,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const uint8_t* base,
 // few-row plans rarely hold more).
 constexpr int kOffsetTiles = 16;
 template <int D, int NT, bool OFF>
-__device__ __forceinline__ void take_offset(RowState<D, NT, false, OFF>& st) {
+__device__ __forceinline__ void take_offset(RowState<D, NT, OFF>& st) {
   static_assert(OFF, "only states with an offset");
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
@@ -636,15 +607,10 @@ __device__ __forceinline__ void take_offset(RowState<D, NT, false, OFF>& st) {
 }
 
 // Row totals of the per-lane sums (the four lanes of a row share the row).
-template <int D, int NT, bool MS, bool OFF>
-__device__ __forceinline__ void finish_sums(RowState<D, NT, MS, OFF>& st) {
+template <int D, int NT, bool OFF>
+__device__ __forceinline__ void finish_sums(RowState<D, NT, OFF>& st) {
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    if constexpr (MS)
-      st.l[nt] = st.lacc[nt][0];
-    else
-      st.l[nt] = xor32_sum(xor16_sum(st.l[nt]));
-  }
+  for (int nt = 0; nt < NT; ++nt) st.l[nt] = xor32_sum(xor16_sum(st.l[nt]));
   if constexpr (OFF) take_offset(st);
 }
 
@@ -652,7 +618,7 @@ __device__ __forceinline__ void finish_sums(RowState<D, NT, MS, OFF>& st) {
 // stores dims [4*DV*G, 4*DV*G + 4*DV) of its row (contiguous), lane G = 0
 // the row's (m, l).
 template <int D, int NT, bool OFF>
-__device__ __forceinline__ void store_partials(RowState<D, NT, false, OFF>& st, int nrows, float* acc_out,
+__device__ __forceinline__ void store_partials(RowState<D, NT, OFF>& st, int nrows, float* acc_out,
                                                float2* ml_out, int lane) {
   constexpr int DV = D / 16;
   const int n = lane & 15, G = lane >> 4;
@@ -675,7 +641,7 @@ __device__ __forceinline__ void store_partials(RowState<D, NT, false, OFF>& st, 
 }
 
 // Running state of a streaming wave over caches of type KV.
-template <int D, int NT, typename KV> using StreamState = RowState<D, NT, false, KV::BITS == 4>;
+template <int D, int NT, typename KV> using StreamState = RowState<D, NT, KV::BITS == 4>;
 
 // The logits' first accumulator of a streaming wave over int4 codes, after
 // its Q^T operands are staged: minus the offset times the sum of the row's q.
@@ -829,7 +795,7 @@ __device__ void decode_block(const PartialsParams& P, int blk, int wave, int lan
 // order (so the result is deterministic): afterwards row r's merged partial
 // is acc_s[r*LD ..], m_s[r], l_s[r] (LD = d + 4), visible to every thread.
 template <int D, int NT, bool OFF>
-__device__ __forceinline__ void merge_waves(RowState<D, NT, false, OFF>& st, float* lds, int wave, int lane) {
+__device__ __forceinline__ void merge_waves(RowState<D, NT, OFF>& st, float* lds, int wave, int lane) {
   constexpr int DV = D / 16;
   constexpr int LD = D + 4;  // padded LDS row
   constexpr int ROWS = NT * kRowsPerTile;
@@ -873,7 +839,7 @@ __device__ __forceinline__ void merge_waves(RowState<D, NT, false, OFF>& st, flo
 // Merge the waves' states and write rows < nrows of the merged partial to
 // acc_out / ml_out.
 template <int D, int NT, bool OFF>
-__device__ __forceinline__ void merge_waves_and_store(RowState<D, NT, false, OFF>& st, float* lds, int nrows,
+__device__ __forceinline__ void merge_waves_and_store(RowState<D, NT, OFF>& st, float* lds, int nrows,
                                                       float* acc_out, float2* ml_out, int wave,
                                                       int lane) {
   constexpr int LD = D + 4;
@@ -1015,154 +981,6 @@ __global__ __launch_bounds__(kThreads) void standard_kernel(PartialsParams P) {
     standard_block<D, NT, KV>(P, blockIdx.x, wave, lane, qw, kl,
                               reinterpret_cast<float*>(lds + QSLOTS));
 }
-
-
-// Context part, many query rows per group: work-group (group gam, key split
-// s, row block rb) of 128 query rows, eight waves with one 16-row query
-// tile each, two work-groups per CU (four waves per SIMD, so one wave's
-// softmax arithmetic overlaps another's matrix products and waits).
-// Each 32-key tile of Kc/Vc is loaded from HBM once per work-group into LDS,
-// already in MFMA operand order (the V^T transpose is done once, on the way
-// in), and all eight waves read it. Each wave stages one eighth of a tile:
-// one K operand (d = 128; the first four waves for d = 64) and one 32-bit
-// word of half of the V^T operands, widening 8-bit or 4-bit codes to bf16 on
-// the way. Tiles are double-buffered in LDS with one barrier per tile, and
-// fetched three tiles ahead into three rotating register sets. Q^T operands stay in registers. Row blocks of one key
-// chunk are scheduled on the same XCD so that they share its L2.
-template <int D, typename KV>
-__device__ __forceinline__ void ctx_large_body(const PartialsParams& P) {
-  constexpr int KS = D / 32;
-  constexpr int DV = D / 16;
-  constexpr int RB = KV::bytes(D);  // bytes per cache row
-  constexpr int KOPS = 2 * KS;    // K operands per tile
-  constexpr int OPS = KOPS + DV;  // operands per tile (16 B per lane each)
-  constexpr int HW = DV / 2;      // V^T operands one wave stages a word of
-  typedef Raw<KV::bytes(8)> KR;   // a lane's 8 elements of its K operand
-  typedef Raw<KV::bytes(HW)> VR;  // a lane's HW elements of a value row
-  typedef typename VR::type VH;
-  __shared__ __attribute__((aligned(16))) u32x4 lds[2 * OPS * 64];
-  const int blk = xcd_logical(blockIdx.x, P.g * P.S_c, P.ctx_row_blocks);
-  const int rb = blk % P.ctx_row_blocks;
-  const int sg = blk / P.ctx_row_blocks;
-  const int s = sg % P.S_c, gam = sg / P.S_c;
-  const int k0 = s * P.ctx_keys;
-  const int nkeys = min(P.m_c, k0 + P.ctx_keys) - k0;
-  const int lane = threadIdx.x & 63, wave = wave_id();
-  const int r = lane & 15, G = lane >> 4;
-  // Buffer resources over the chunk's keys [k0, k0 + nkeys): rows past it
-  // load as zero with no memory access and no branch. Offsets count from k0.
-  const size_t chunk = ((size_t)gam * P.m_c + k0) * RB;
-  const __amdgpu_buffer_rsrc_t rk = rows_rsrc(P.Kc + chunk, nkeys, RB);
-  const __amdgpu_buffer_rsrc_t rv = rows_rsrc(P.Vc + chunk, nkeys, RB);
-  const float scale_log2 = unit_scale_log2(P, gam);
-  const int M = P.M, p = P.p, h = P.h;
-  const int row0 = rb * kLargeRowsPerBlock + wave * kRowsPerTile;
-  auto slot = [&](int buf, int op) -> u32x4* { return lds + (buf * OPS + op) * 64; };
-  const bool has_k = wave < KOPS;              // wave-uniform
-  const int ka = wave / KS, kss = wave % KS;   // the K operand this wave stages
-  const int vw = wave & 3, vh = wave >> 2;     // its V^T word and operand half
-
-  // Registers of a tile in flight: this wave's K operand and two value-row halves.
-  struct Stage {
-    typename KR::type k;
-    VH v[2];
-  };
-  auto fetch = [&](Stage& g, int key0) {  // keys past the chunk load as zero
-    if (has_k)
-      g.k = KR::load(rk, boff((uint32_t)(key0 + qk_key(ka, r)) * RB +
-                              (uint32_t)KV::bytes(kss * 32 + G * 8)));
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-      g.v[c] = VR::load(rv, boff((uint32_t)(key0 + 4 * (2 * vw + c) + G) * RB +
-                                 (uint32_t)KV::bytes(DV * r + vh * HW)));
-  };
-  auto stage = [&](const Stage& g, int buf) {
-    if (has_k) slot(buf, wave)[lane] = Widen8<KV>::run(g.k);
-    // word vw of V^T operand vh*HW + t = keys 4(2vw) + G, 4(2vw+1) + G at dim DV*r + vh*HW + t
-#pragma unroll
-    for (int t = 0; t < HW; ++t)
-      reinterpret_cast<uint32_t*>(slot(buf, KOPS + vh * HW + t) + lane)[vw] =
-          value_pair<KV>(g.v[0], g.v[1], t);
-  };
-
-  // Q first, then the first two tiles: the wait for the first tile then also
-  // covers Q, so no wait inside the loop reaches past the set in flight.
-  u32x4 qop[1][KS];
-  load_q<D, 1>(qop, [&](int rr) -> const uint16_t* {
-    const int row = row0 + rr;
-    if (row >= M) return nullptr;
-    const int i = row / p, jp = row - i * p;
-    return P.q + ((size_t)i * h + (size_t)gam * p + jp) * D;
-  }, P.q_sign, lane);
-  constexpr int T = kTileKeys;
-  Stage S0, S1, S2;
-  fetch(S0, 0);
-  fetch(S1, T);
-  fetch(S2, 2 * T);
-  RowState<D, 1, true> st;
-  st.init();
-  const bool rows = row0 < M;  // wave-uniform: waves past the last row only stage
-  stage(S0, 0);
-  __syncthreads();
-  // Tile `key` (in LDS buffer buf) is consumed while the next two tiles are
-  // in flight in two register sets and the one after them is issued into
-  // the third (the set tile `key` came from); fetches past the chunk are
-  // unconditional (they read zeros), so every wait covers exactly one set.
-  // The loop runs six tiles per turn while a seventh follows (a single exit
-  // at the bottom keeps the waits exact); the last one to six tiles are the
-  // tail.
-  auto step = [&](int key, int buf, Stage& spare, Stage& next, bool stage_next) {
-    fetch(spare, key + 3 * T);
-    if (rows)
-      tile_update(st, [&](int a, int ss) { return slot(buf, a * KS + ss)[lane]; },
-                        [&](int t) { return slot(buf, KOPS + t)[lane]; },
-                        [&](int, int ss) { return qop[0][ss]; }, nkeys - key, 1, 0,
-                        scale_log2, lane);
-    if (stage_next) {
-      // The other buffer was last read in the previous step, before the
-      // barrier that ended it.
-      stage(next, buf ^ 1);
-      __syncthreads();
-    }
-  };
-  int key = 0;
-  for (; key + 6 * T < nkeys; key += 6 * T) {
-    step(key, 0, S0, S1, true);
-    step(key + T, 1, S1, S2, true);
-    step(key + 2 * T, 0, S2, S0, true);
-    step(key + 3 * T, 1, S0, S1, true);
-    step(key + 4 * T, 0, S1, S2, true);
-    step(key + 5 * T, 1, S2, S0, true);
-  }
-  step(key, 0, S0, S1, key + T < nkeys);
-  if (key + T < nkeys) step(key + T, 1, S1, S2, key + 2 * T < nkeys);
-  if (key + 2 * T < nkeys) step(key + 2 * T, 0, S2, S0, key + 3 * T < nkeys);
-  if (key + 3 * T < nkeys) step(key + 3 * T, 1, S0, S1, key + 4 * T < nkeys);
-  if (key + 4 * T < nkeys) step(key + 4 * T, 0, S1, S2, key + 5 * T < nkeys);
-  if (key + 5 * T < nkeys) step(key + 5 * T, 1, S2, S0, false);
-
-  finish_sums(st);
-  const int row = row0 + r;
-  if (row < M) {
-    const size_t prow = ((size_t)gam * P.S_c + s) * P.M + row;
-    float* dst = P.ctx_acc + prow * D + 4 * DV * G;
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int t4 = 0; t4 < DV; t4 += 4)
-        *reinterpret_cast<f32x4*>(dst + DV * j + t4) =
-            f32x4{st.acc[0][t4][j], st.acc[0][t4 + 1][j], st.acc[0][t4 + 2][j],
-                  st.acc[0][t4 + 3][j]};
-    if (G == 0) P.ctx_ml[prow] = float2{st.mref[0], st.l[0]};
-  }
-}
-
-template <int D, typename KV>
-__global__ __launch_bounds__(kLargeThreads) __attribute__((amdgpu_waves_per_eu(4))) void
-ctx_large_kernel(PartialsParams P) {
-  ctx_large_body<D, KV>(P);
-}
-
 
 // ---------------------------------------------------------------------------
 // Context part, many query rows per group (any cache type), on
@@ -1922,19 +1740,6 @@ hipError_t launch_ctx_wide(const PartialsParams& P, int kv, int dec_tiles, hipSt
                                               : launch_ctx_wide_n<D, 1>(P, kv, stream, ev);
 }
 
-template <int D>
-hipError_t launch_ctx_large_d(const PartialsParams& P, int kv, hipStream_t stream,
-                              const LaunchEvents& ev) {
-  const int grid = P.n_ctx_blocks;
-  switch (kv) {
-    case kKvBf16: return launch(ctx_large_kernel<D, KvBf16>, grid, kLargeThreads, stream, ev, P);
-    case kKvFp8: return launch(ctx_large_kernel<D, KvFp8>, grid, kLargeThreads, stream, ev, P);
-    case kKvInt8: return launch(ctx_large_kernel<D, KvInt8>, grid, kLargeThreads, stream, ev, P);
-    case kKvInt4: return launch(ctx_large_kernel<D, KvInt4>, grid, kLargeThreads, stream, ev, P);
-    default: return hipErrorInvalidValue;
-  }
-}
-
 // Decode-cache append (the decode cache holds the keys and values of the
 // previous decoding steps, Section 3.1): work-group i copies sample i's n new
 // rows of every group to rows len_i .. len_i + n - 1 of its decode cache and
@@ -2009,13 +1814,9 @@ hipError_t scratch_address(int device, void** ptr) {
 hipError_t launch_ctx_large(const PartialsParams& P, int d, int kv, int dec_tiles,
                             hipStream_t stream, const LaunchEvents& ev) {
   if (P.n_ctx_blocks == 0) return hipSuccess;
-  if (P.ctx_wide) {
-    if (d == 128) return launch_ctx_wide<128>(P, kv, dec_tiles, stream, ev);
-    if (d == 64) return launch_ctx_wide<64>(P, kv, dec_tiles, stream, ev);
-    return hipErrorInvalidValue;
-  }
-  if (P.n_dec_blocks > 0 || d != 128) return hipErrorInvalidValue;
-  return launch_ctx_large_d<128>(P, kv, stream, ev);
+  if (d == 128) return launch_ctx_wide<128>(P, kv, dec_tiles, stream, ev);
+  if (d == 64) return launch_ctx_wide<64>(P, kv, dec_tiles, stream, ev);
+  return hipErrorInvalidValue;
 }
 hipError_t launch_standard(const PartialsParams& P, int d, int kv, int tiles,
                            hipStream_t stream, const LaunchEvents& ev) {

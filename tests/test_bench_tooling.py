@@ -97,10 +97,10 @@ def test_profile_summary_scales_counters_by_the_copy(tmp_path):
 
 
 def test_profile_summary_of_the_context_kernel(tmp_path):
-    """--kernel ctx_large records the many-row context kernel's counters under
+    """--kernel ctx_wide records the many-row context kernel's counters under
     its own name."""
     root = str(tmp_path)
-    ctx = "void bifattn::ctx_large_kernel<128, KvBf16>(bifattn::PartialsParams)"
+    ctx = "void bifattn::ctx_wide_kernel<128, 8, 2, 128, KvBf16, 1>(bifattn::PartialsParams)"
     _write_csv(os.path.join(root, "stats", "run_kernel_stats.csv"),
                ["Name", "Calls", "AverageNs", "MinNs", "MaxNs", "Percentage"],
                [[ctx, 2, 50000, 50000, 50000, 60.0], [PART, 2, 20000, 20000, 20000, 40.0]])
@@ -116,9 +116,9 @@ def test_profile_summary_of_the_context_kernel(tmp_path):
                [[COPY, "WRITE_SIZE", kib], [PART, "WRITE_SIZE", 1.0], [ctx, "WRITE_SIZE", 64.0]])
     out = tmp_path / "out"
     bench.summarize_profile(str(tmp_path / "stats"), str(tmp_path / "fetch"), str(tmp_path / "write"),
-                            "mqa_b128_mc16k_md512", str(out), 0, 1, kernel="ctx_large")
-    rec = json.load(open(out / "traffic_ctx_large_mqa_b128_mc16k_md512.json"))
-    assert "ctx_large_kernel" in rec["kernel"]
+                            "mqa_b128_mc16k_md512", str(out), 0, 1, kernel="ctx_wide")
+    rec = json.load(open(out / "traffic_ctx_wide_mqa_b128_mc16k_md512.json"))
+    assert "ctx_wide_kernel" in rec["kernel"]
     assert rec["hbm_fetch_bytes_per_launch"] == pytest.approx(4096.0 * 1024 * 2)
     assert rec["trace_avg_us_all_launches"] == pytest.approx(50.0)
 

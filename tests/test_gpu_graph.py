@@ -16,9 +16,8 @@ pytestmark = pytest.mark.gpu
 # b, h, g, d, m_c, m_d_max, n, kv, fork: the standard path (tiny layer), the
 # fused few-row launch, the many-row context kernel then the decode launch,
 # both in one launch, several tokens, an 8-bit cache with scales; and the side
-# stream (units of more than 32 query rows), which takes eight- and four-wave
-# work-groups, the kernel of 16-row waves (below 128 rows per group), codes, and
-# d = 64.
+# stream (units of more than 32 query rows) with eight- and four-wave
+# work-groups, fewer rows than it takes by itself, codes, and d = 64.
 CASES = [
     (4, 4, 4, 64, 128, 16, 1, "bf16", None),
     (8, 32, 32, 128, 2048, 256, 1, "bf16", None),

@@ -281,30 +281,27 @@ def test_side_stream_decode(case, monkeypatch):
     """Many-row plans may run the decode work-groups beside the context ones:
     in the 32x32 kernel's launch for units of at most 32 query rows, else on a
     side stream (the call's stream waits for it before the combine). Forced on
-    and off with either context kernel, every output matches the oracle, and
-    with the same kernel the two are bitwise equal when the plans split the
-    context alike."""
+    and off, every output matches the oracle, and the two are bitwise equal
+    when the plans split the context alike."""
     b, h, g, d, m_c, m_d, n, kv = case
     x = workloads.make_inputs(b, h, g, d, m_c, m_d, seed=1200 + m_c, ragged=True, n=n, kv=kv)
     ref = oracle.attention(**x)
-    for wide in ("0", "1") if d == 128 else ("1",):
-        monkeypatch.setenv("BIFATTN_CTX_WIDE", wide)
-        runs = []
-        for fork in ("0", "1"):
-            monkeypatch.setenv("BIFATTN_FORK", fork)
-            with bif.Plan(b, h, g, d, m_c, m_d, n=n, kv=kv) as plan:
-                info = plan.info()
-                if b * (h // g) * n > 64:  # many rows per group (else the few-row launch)
-                    one_launch = wide == "1" and h // g * n <= 32
-                    assert info["side_stream"] == int(fork == "1" and not one_launch)
-                    assert info["fused"] == int(fork == "1" and one_launch)
-                    assert info["ctx_kernel"] == (2 if wide == "1" else 1)
-                out = run_decode(x, plan=plan)
-            _report(f"side stream {case} wide={wide} fork={fork}",
-                    *assert_parity(out, ref, f"{case} wide={wide} fork={fork}", x=x))
-            runs.append((info["ctx_splits"], out))
-        if runs[0][0] == runs[1][0]:
-            assert np.array_equal(runs[0][1], runs[1][1])
+    runs = []
+    for fork in ("0", "1"):
+        monkeypatch.setenv("BIFATTN_FORK", fork)
+        with bif.Plan(b, h, g, d, m_c, m_d, n=n, kv=kv) as plan:
+            info = plan.info()
+            if b * (h // g) * n > 64:  # many rows per group (else the few-row launch)
+                one_launch = h // g * n <= 32
+                assert info["side_stream"] == int(fork == "1" and not one_launch)
+                assert info["fused"] == int(fork == "1" and one_launch)
+                assert info["ctx_kernel"] == 2
+            out = run_decode(x, plan=plan)
+        _report(f"side stream {case} fork={fork}",
+                *assert_parity(out, ref, f"{case} fork={fork}", x=x))
+        runs.append((info["ctx_splits"], out))
+    if runs[0][0] == runs[1][0]:
+        assert np.array_equal(runs[0][1], runs[1][1])
 
 
 def test_plan_rule_for_large_decode_parts(monkeypatch):
@@ -313,7 +310,7 @@ def test_plan_rule_for_large_decode_parts(monkeypatch):
     units have at most 32 query rows; else on the side stream, with the context
     on five eighths of the CUs from 256 rows per group and on about one
     four-wave work-group per CU with 128 to 255."""
-    for var in ("BIFATTN_FORK", "BIFATTN_CTX_WIDE", "BIFATTN_CTX_WGS"):
+    for var in ("BIFATTN_FORK", "BIFATTN_CTX_WGS"):
         monkeypatch.delenv(var, raising=False)
     with bif.Plan(256, 32, 8, 128, 32768, 1024) as plan:  # 1024 rows per group
         info = plan.info()
@@ -328,8 +325,11 @@ def test_plan_rule_for_large_decode_parts(monkeypatch):
             info = plan.info()
             assert info["fused"] == 0 and info["side_stream"] == 1 and info["ctx_kernel"] == 2
             assert info["ctx_blocks"] < blocks + 32 * info["ctx_row_blocks"]  # rounded up to splits
-    with bif.Plan(8, 1280, 32, 128, 4096, 16) as plan:  # a small decode part follows
-        assert plan.info()["fused"] == plan.info()["side_stream"] == 0
+    # a small decode part follows the context kernel, and a large one beside 80 rows
+    for shape in ((8, 1280, 32, 128, 4096, 16), (2, 1280, 32, 128, 1024, 1024)):
+        with bif.Plan(*shape) as plan:
+            info = plan.info()
+            assert info["fused"] == info["side_stream"] == 0 and info["ctx_kernel"] == 2
 
 
 def test_largest_context_rows_are_addressed():
@@ -386,10 +386,9 @@ def test_split_launch_equals_fused(case, monkeypatch):
     _report(f"split launch {case}", *assert_parity(split, oracle.attention(**x), str(case), x=x))
 
 
-# Many-row context shapes for both context kernels (the 32x32 MFMA kernel of
-# 32-row waves, and the kernel of 16-row waves): 128- and 64-key stages,
-# ragged last chunks, row blocks whose last waves hold no rows, several
-# tokens, grouped heads, and four-wave work-groups (fewer than 256 rows).
+# Many-row context shapes: 128- and 64-key stages, ragged last chunks, row
+# blocks whose last waves hold no rows, several tokens, grouped heads, and
+# four-wave work-groups.
 WIDE_CASES = [
     # b, h, g, d, m_c, m_d_max, n
     (48, 32, 1, 128, 50000, 64, 1),   # 1280-key chunks: 128-key stages, ragged last chunk
@@ -407,26 +406,23 @@ def test_many_row_context_kernels(case, monkeypatch):
     x = workloads.make_inputs(b, h, g, d, m_c, m_d, seed=1600 + m_c, ragged=True, n=n)
     ref = oracle.attention(**x)
     monkeypatch.setenv("BIFATTN_FORK", "0")
-    for wide in ("1", "0"):
-        monkeypatch.setenv("BIFATTN_CTX_WIDE", wide)
-        with bif.Plan(b, h, g, d, m_c, m_d, n=n, path="bifurcated") as plan:
-            info = plan.info()
-            print(f"[case] many-row {case} wide={wide} {info}", flush=True)
-            out = run_decode(x, plan=plan)
-        _report(f"many-row {case} wide={wide}", *assert_parity(out, ref, f"{case} wide={wide}", x=x))
-
+    with bif.Plan(b, h, g, d, m_c, m_d, n=n, path="bifurcated") as plan:
+        print(f"[case] many-row {case} {plan.info()}", flush=True)
+        out = run_decode(x, plan=plan)
+    _report(f"many-row {case}", *assert_parity(out, ref, f"{case}", x=x))
 
 
 @pytest.mark.parametrize("pattern", ["growing", "needle"])
-@pytest.mark.parametrize("case", [(48, 32, 1, 128, 6000, 64), (64, 32, 8, 128, 3000, 100)],
+@pytest.mark.parametrize("case", [(48, 32, 1, 128, 6000, 64), (64, 32, 8, 128, 3000, 100),
+                                  (48, 32, 1, 64, 9000, 64), (40, 8, 2, 64, 3000, 100)],
                          ids=lambda c: "b%d_h%d_g%d_d%d_mc%d_md%d" % c)
 def test_many_row_context_with_rising_logits(case, pattern, monkeypatch):
     """Context keys whose logits keep rising past the running reference
     maximum: key rows whose norm grows from 1x to 4x over every 128 keys (the
     row maxima rise by more than 2^8 several times inside a key chunk), or
     one key row scaled 8x in the middle of the context (a jump far above the
-    reference). Both many-row kernels take their rescale paths inside their
-    chunks and still match the oracle. The softmax is sharpened on purpose,
+    reference). The many-row kernel takes its rescale path inside its chunks
+    and still matches the oracle. The softmax is sharpened on purpose,
     so single weights carry whole rows: the max-abs gate is the contract
     bound and the values are halved (exactly), which keeps a dominant
     weight's bf16 rounding (2^-9 of its value row) well inside it; the
@@ -448,32 +444,27 @@ def test_many_row_context_with_rising_logits(case, pattern, monkeypatch):
         x[name] = workloads.f32_to_bf16_bits((x[name].astype(np.uint32) << 16).view(np.float32) * 0.5)
     ref = oracle.attention(**x)
     monkeypatch.setenv("BIFATTN_FORK", "0")
-    for wide in ("1", "0"):
-        monkeypatch.setenv("BIFATTN_CTX_WIDE", wide)
-        with bif.Plan(b, h, g, d, m_c, m_d, path="bifurcated") as plan:
-            print(f"[case] rising logits {pattern} {case} wide={wide} {plan.info()}", flush=True)
-            out = run_decode(x, plan=plan)
-        _report(f"rising logits {pattern} {case} wide={wide}",
-                *assert_parity(out, ref, f"{pattern} {case} wide={wide}", x=x,
-                               gate_max_abs=CONTRACT_MAX_ABS))
+    with bif.Plan(b, h, g, d, m_c, m_d, path="bifurcated") as plan:
+        info = plan.info()
+        print(f"[case] rising logits {pattern} {case} {info}", flush=True)
+        assert info["ctx_kernel"] == 2
+        out = run_decode(x, plan=plan)
+    _report(f"rising logits {pattern} {case}",
+            *assert_parity(out, ref, f"{pattern} {case}", x=x, gate_max_abs=CONTRACT_MAX_ABS))
 
 
 @pytest.mark.parametrize("kv", ["fp8_e4m3", "int8", "int4"])
 @pytest.mark.parametrize("case", WIDE_CASES, ids=lambda c: "b%d_h%d_g%d_d%d_mc%d_md%d_n%d" % c)
 def test_many_row_context_kernels_code_caches(case, kv, monkeypatch):
-    """Both many-row context kernels over 8-bit and int4 caches: the 32x32
-    kernel stages the codes through registers and widens them into its LDS
-    stages, the 16x16 kernel widens them while staging its tiles."""
+    """The many-row context kernel over 8-bit and int4 caches: it stages the codes
+    through registers and widens them into its LDS stages."""
     b, h, g, d, m_c, m_d, n = case
     x = workloads.make_inputs(b, h, g, d, m_c, m_d, seed=1650 + m_c, ragged=True, n=n, kv=kv)
     ref = oracle.attention(**x)
     monkeypatch.setenv("BIFATTN_FORK", "0")
-    for wide in ("1", "0"):
-        monkeypatch.setenv("BIFATTN_CTX_WIDE", wide)
-        with bif.Plan(b, h, g, d, m_c, m_d, n=n, kv=kv, path="bifurcated") as plan:
-            info = plan.info()
-            assert info["ctx_kernel"] == (2 if wide == "1" else 1)
-            print(f"[case] many-row {kv} {case} wide={wide} {info}", flush=True)
-            out = run_decode(x, plan=plan)
-        _report(f"many-row {kv} {case} wide={wide}",
-                *assert_parity(out, ref, f"{kv} {case} wide={wide}", x=x))
+    with bif.Plan(b, h, g, d, m_c, m_d, n=n, kv=kv, path="bifurcated") as plan:
+        info = plan.info()
+        assert info["ctx_kernel"] == 2
+        print(f"[case] many-row {kv} {case} {info}", flush=True)
+        out = run_decode(x, plan=plan)
+    _report(f"many-row {kv} {case}", *assert_parity(out, ref, f"{kv} {case}", x=x))
