@@ -234,3 +234,50 @@ def test_many_row_splits_use_the_slots_there_are():
     assert 384 < blocks(40, 40, 40, 64, 12000, 100) <= 768       # one row block: 320 -> 480 or so
     assert blocks(27, 16, 8, 128, 35226, 0, n=2) <= 256           # was 296: 44.0 us, now 36.2
     assert 512 < blocks(43, 2048, 32, 64, 919, 0, kv="int4") <= 768  # was two rounds of eight waves
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [
+    # b, h, g, d, m_c, m_d, n, kv: 65 to 80 MiB of partials with the plan's own
+    # splits, 43 to 55 with longer chunks
+    (130, 256, 8, 64, 9303, 32, 1, "int4"),
+    (30, 536, 67, 64, 8851, 5, 2, "int8"),
+    (52, 300, 60, 128, 14829, 11, 1, "int8"),
+], ids=lambda c: "b%d_h%d_g%d_d%d_mc%d_md%d_n%d_%s" % c)
+def test_noalloc_with_longer_chunks(case):
+    """A problem whose partials pass the scratch with its plan's splits and fit it
+    with longer chunks: sampled rows against the oracle, every row against the
+    plan's result (the two round their weights apart: 2^-9 / sqrt(3) each)."""
+    import numpy as np
+    import torch
+    from .gpu_util import sample_rows, to_device
+    b, h, g, d, m_c, m_d, n, kv = case
+    rng = np.random.default_rng(2600 + m_c)
+    cols, std = (d // 2, 21.25 ** 0.5) if kv == "int4" else (d, 73.9)  # of uniform codes
+    codes = lambda *s: rng.integers(0, 256, (*s, cols), dtype=np.uint8)
+    q = rng.standard_normal((b, h, d) if n == 1 else (b, h, n, d), dtype=np.float32)
+    x = dict(q=workloads.f32_to_bf16_bits(q), Kc=codes(g, m_c), Vc=codes(g, m_c),
+             Kd=codes(b, g, m_d), Vd=codes(b, g, m_d),
+             lens=rng.integers(n, m_d + 1, b).astype(np.int32), kv=kv,
+             k_scale=np.full(g, 1 / std, np.float32), v_scale=np.full(g, 1 / std, np.float32))
+    dev = to_device(x)
+    args = [dev[k] for k in ("q", "Kc", "Vc", "Kd", "Vd", "lens", "k_scale", "v_scale")]
+    outs = [torch.full(tuple(x["q"].shape), float("nan"), device="cuda") for _ in range(2)]
+    with bif.Plan(b, h, g, d, m_c, m_d, n=n, kv=kv, path="bifurcated") as plan:
+        info = plan.info()
+        print(f"[case] {case} {info}", flush=True)
+        rows = b * (h // g) * n * g
+        parts = info["ctx_splits"] + info["dec_splits"]
+        assert rows * parts * (d + 2) * 4 > bif.NOALLOC_SCRATCH_BYTES
+        bif.bifattn_decode_scaled(plan, *args, outs[0])
+        torch.cuda.synchronize()
+    dims = bif.noalloc_dims(b, h, g, d, m_c, m_d, n=n, kv=kv, path="bifurcated")
+    bif.bifattn_decode_noalloc(dims, *args, outs[1])
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(outs[1]).all())
+    rel = float((outs[0] - outs[1]).norm() / outs[0].norm())
+    assert 0 < rel < 4e-3, rel
+    ri, rj = sample_rows(b, h, x["lens"], 24, seed=7)
+    rt = np.arange(ri.size, dtype=np.int32) % n
+    out = outs[1].cpu().double().numpy().reshape(b, h, n, d)[ri, rj, rt]
+    assert_parity(out, oracle.attention_rows(**x, rows_i=ri, rows_j=rj, rows_t=rt), str(case), x=x)
