@@ -1,6 +1,7 @@
-"""Infinite cache values: a value of +-inf under a positive softmax weight makes
-its output dimension +-inf and leaves every other one alone, however many
-partials a row has (MI355X only)."""
+"""Infinite cache values and NaN queries: a value of +-inf under a positive
+softmax weight makes its output dimension +-inf and leaves every other one
+alone, however many partials a row has; a NaN query reaches no other row
+(MI355X only)."""
 import numpy as np
 import pytest
 
@@ -43,3 +44,28 @@ def test_infinite_values(splits, b, d, monkeypatch):
     assert special.sum() == 2 * b * h + 2 * h
     assert np.array_equal(out[special], ref[special])
     assert_parity(np.where(special, 0, out), np.where(special, 0, ref), f"inf {splits} {b} {d}", x=x)
+
+
+@pytest.mark.parametrize("case", [
+    # b, h, g, d, m_c, m_d, n, kv: few rows; many rows with four and eight waves
+    (3, 8, 2, 128, 300, 40, 1, "bf16"),
+    (3, 8, 2, 64, 300, 40, 1, "int4"),
+    (40, 8, 2, 128, 700, 40, 1, "bf16"),
+    (40, 8, 2, 64, 700, 40, 1, "bf16"),
+    (50, 16, 2, 64, 9000, 40, 1, "int8"),
+    (40, 4, 2, 64, 900, 40, 2, "bf16"),
+], ids=lambda c: "b%d_h%d_g%d_d%d_mc%d_md%d_n%d_%s" % c)
+@pytest.mark.parametrize("path", ["standard", "bifurcated"])
+def test_a_nan_query_stays_in_its_rows(case, path):
+    b, h, g, d, m_c, m_d, n, kv = case
+    x = workloads.make_inputs(b, h, g, d, m_c, m_d, seed=2400 + m_c, n=n, kv=kv)
+    ref = oracle.attention(**x)
+    x["q"] = x["q"].copy()
+    x["q"][1] = 0x7FC0           # a whole sample
+    x["q"][b - 1, 0, ..., 5] = 0x7FC0  # one element of one head
+    bad = np.zeros(ref.shape, bool)
+    bad[1] = bad[b - 1, 0] = True
+    print(f"[case] nan query {case} {path}", flush=True)
+    out = run_path(x, path)
+    assert np.isnan(out[bad]).all()
+    assert_parity(np.where(bad, 0, out), np.where(bad, 0, ref), f"nan query {case}", x=x)

@@ -468,3 +468,26 @@ def test_many_row_context_kernels_code_caches(case, kv, monkeypatch):
         print(f"[case] many-row {kv} {case} {info}", flush=True)
         out = run_decode(x, plan=plan)
     _report(f"many-row {kv} {case}", *assert_parity(out, ref, f"{kv} {case}", x=x))
+
+
+@pytest.mark.parametrize("kv", ["bf16", "int8"])
+@pytest.mark.parametrize("case", [(40, 8, 2, 64, 700, 0), (17, 2, 1, 64, 333, 0), (90, 16, 2, 64, 9000, 0)],
+                         ids=lambda c: "b%d_h%d_g%d_d%d_mc%d_md%d" % c)
+def test_rounded_weights_are_divided_by_their_own_sum(case, kv):
+    """Many rows, d = 64: with every value 1 the output is a sum of rounded weights
+    over itself. Both are fp32 sums of at most ~300 terms of a split, so it is 1
+    within 300 * 2^-24 ~ 2e-5; over the unrounded weights' sum it would be off by
+    2^-9 / sqrt(3 N / e), 2e-5 to 1e-4 here on average, four times that at most
+    rows."""
+    b, h, g, d, m_c, m_d = case
+    x = workloads.make_inputs(b, h, g, d, m_c, m_d, seed=2700 + m_c, kv=kv)
+    if kv == "bf16":
+        x["Vc"] = np.full_like(x["Vc"], 0x3F80)
+    else:
+        x["Vc"], x["v_scale"] = np.full_like(x["Vc"], 1), np.ones_like(x["v_scale"])
+    with bif.Plan(b, h, g, d, m_c, m_d, kv=kv, path="bifurcated") as plan:
+        assert plan.info()["ctx_kernel"] == 2
+        out = run_decode(x, plan=plan)
+    err = float(np.max(np.abs(out - 1)))
+    print(f"[parity] ones {case} {kv}: max_abs={err:.3e}", flush=True)
+    assert err <= 2e-5, err
