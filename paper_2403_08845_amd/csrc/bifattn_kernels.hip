@@ -1122,7 +1122,7 @@ template <int D> constexpr int wide_stage_bytes(int NB, int SK) {
   return NB * SK * (Wide<D>::KROW + Wide<D>::VROW);
 }
 
-template <int D, int NW, int NB, int SK, typename KV>
+template <int D, int NW, int NB, int SK, typename KV, bool kRounded>
 __device__ __forceinline__ void ctx_wide_block(const PartialsParams& P, unsigned char* lds) {
   constexpr int RB = Wide<D>::RB, KSTEPS = Wide<D>::KSTEPS, DB = Wide<D>::DB;
   constexpr int KROW = Wide<D>::KROW, VROW = Wide<D>::VROW;
@@ -1274,16 +1274,15 @@ __device__ __forceinline__ void ctx_wide_block(const PartialsParams& P, unsigned
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
   float mref = kNegInf, lsum = 0.f;
-  // d = 64: the sums of the rounded weights, the weights the values are
+  // kRounded: the sums of the rounded weights, the weights the values are
   // multiplied by, on v_mfma_f32_16x16x32_bf16. As its B operand a lane's 8
   // weights are column lane % 16, k-slots 8 (lane / 16) ..: rows j and j + 16 of
   // the block share a column, and alternate groups of four rows of A pick one
   // or the other, so that all four elements of a lane's C are its own row's sum
   // over both halves. Dividing by them instead of the unrounded weights' sum
-  // (d = 128) takes 0.1% to 1.3% off the error against 64 bits, for 0.3% to 2% of the
-  // step (adding up the rounded weights in the vector unit: 2% to 7%). A row
+  // takes 0.1% to 1.3% off the error against 64 bits, for 0.3% to 2% of the step
+  // (adding up the rounded weights in the vector unit: 2% to 7%). A row
   // whose partner holds NaN, which 0 does not pick out, takes the other sum.
-  constexpr bool kRounded = D == 64;
   const uint32_t pick = ((lane >> 2) & 1) == ((lane >> 4) & 1) ? 0x3F803F80u : 0u;  // bf16 1.0 or 0
   f32x4 lrow = {0.f, 0.f, 0.f, 0.f};
   const bool active = row0 < M;  // wave-uniform
@@ -1422,7 +1421,7 @@ __device__ __forceinline__ void ctx_wide_block(const PartialsParams& P, unsigned
 // Against a launch behind it or on a second stream (us per step): MQA, 128
 // samples over 16k, 65.2 -> 56.7; 4 draft tokens, 32 samples over 8k, 94.5 ->
 // 81.4; ragged GQA, 256 samples over 32k, 221.6 -> 216.9.
-template <int D, int NW, int NB, int SK, typename KV, int NTD>
+template <int D, int NW, int NB, int SK, typename KV, int NTD, bool R>
 __device__ __forceinline__ void ctx_wide_body(const PartialsParams& P) {
   constexpr int QB = NTD * (D / 32) * 64 * 16;  // bytes of a decode wave's Q^T operands
   constexpr int KB = kTileKeys * D * 2;         // and of its K tile
@@ -1430,7 +1429,7 @@ __device__ __forceinline__ void ctx_wide_body(const PartialsParams& P) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS];
   const int bid = blockIdx.x;
   if (bid < P.n_ctx_blocks) {
-    ctx_wide_block<D, NW, NB, SK, KV>(P, lds);
+    ctx_wide_block<D, NW, NB, SK, KV, R>(P, lds);
     return;
   }
   const int lane = threadIdx.x & 63, wave = wave_id();
@@ -1442,10 +1441,10 @@ __device__ __forceinline__ void ctx_wide_body(const PartialsParams& P) {
   }
 }
 
-template <int D, int NW, int NB, int SK, typename KV, int NTD>
+template <int D, int NW, int NB, int SK, typename KV, int NTD, bool R = D == 64>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) void
 ctx_wide_kernel(PartialsParams P) {
-  ctx_wide_body<D, NW, NB, SK, KV, NTD>(P);
+  ctx_wide_body<D, NW, NB, SK, KV, NTD, R>(P);
 }
 
 // Grid: n_ctx_small_blocks work-groups of the few-row context path, then
@@ -1732,8 +1731,15 @@ hipError_t launch_ctx_wide_kv(const PartialsParams& P, hipStream_t stream,
         return launch(ctx_wide_kernel<D, 8, kDirect ? 3 : 2, 64, KV, NTD>, grid, 512, stream, ev, P);
     return launch(ctx_wide_kernel<D, 8, 2, 128, KV, NTD>, grid, 512, stream, ev, P);
   }
-  if (P.ctx_wide == 4)
+  if (P.ctx_wide == 4) {
+    // Rounded weights' sums for every plan of d = 64 and for one part-filled row
+    // block of d = 128: those plans had them with the kernels before this one,
+    // and full d = 128 blocks never had.
+    if constexpr (D == 128)
+      if (P.M > 64 && P.M < 128)
+        return launch(ctx_wide_kernel<D, 4, 2, 64, KV, NTD, true>, grid, 256, stream, ev, P);
     return launch(ctx_wide_kernel<D, 4, 2, 64, KV, NTD>, grid, 256, stream, ev, P);
+  }
   return hipErrorInvalidValue;
 }
 

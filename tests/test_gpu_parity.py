@@ -471,10 +471,11 @@ def test_many_row_context_kernels_code_caches(case, kv, monkeypatch):
 
 
 @pytest.mark.parametrize("kv", ["bf16", "int8"])
-@pytest.mark.parametrize("case", [(40, 8, 2, 64, 700, 0), (17, 2, 1, 64, 333, 0), (90, 16, 2, 64, 9000, 0)],
+@pytest.mark.parametrize("case", [(40, 8, 2, 64, 700, 0), (17, 2, 1, 64, 333, 0), (90, 16, 2, 64, 9000, 0),
+                                  (65, 2, 2, 128, 700, 0), (31, 8, 2, 128, 3000, 0)],
                          ids=lambda c: "b%d_h%d_g%d_d%d_mc%d_md%d" % c)
 def test_rounded_weights_are_divided_by_their_own_sum(case, kv):
-    """Many rows, d = 64: with every value 1 the output is a sum of rounded weights
+    """Many rows of d = 64, 65 to 127 of d = 128: with every value 1 the output is a sum of rounded weights
     over itself. Both are fp32 sums of at most ~300 terms of a split, so it is 1
     within 300 * 2^-24 ~ 2e-5; over the unrounded weights' sum it would be off by
     2^-9 / sqrt(3 N / e), 2e-5 to 1e-4 here on average, four times that at most
