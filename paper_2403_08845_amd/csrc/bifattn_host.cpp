@@ -24,6 +24,7 @@ struct bifattn_plan_s {
   int dec_tiles = 1;
   int ctx_keys = 0, S_c = 0, ctx_row_blocks = 1, n_ctx_blocks = 0, n_ctx_small_blocks = 0;
   int ctx_wide = 0;  // many-row path: waves per work-group of its context kernel (8 or 4)
+  double many_us = -1.0;  // many_row_split's estimate, where it chose the split
   int dec_keys = 0, S_d = 0, n_dec_blocks = 0;
   int rep_keys = 0, S_r = 0, n_rep_blocks = 0;
   int fused = 1;       // context and decode work-groups in one launch
@@ -226,7 +227,8 @@ double standard_us(const bifattn_plan_s* P) {
 }
 double bifurcated_us(const bifattn_plan_s* P) {
   const bifattn_dims_t& d = P->dims;
-  if (P->ctx_mode == kCtxLarge) return 4.5 + 1.17 * many_row_split(P, P->M).us;
+  if (P->ctx_mode == kCtxLarge)
+    return 4.5 + 1.17 * (P->many_us >= 0.0 ? P->many_us : many_row_split(P, P->M).us);
   const bool half = d.d == 64;
   return 8.0 + (half ? 4.2e-3 : 7.0e-3) * ((double)d.m_c / P->S_c) +
          (half ? 1.0e-3 : 4.0e-3) * std::min(P->dec_keys, d.m_d_max) +
@@ -337,6 +339,7 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
     ManySplit split;
     if (one_launch && wgs == 0) {
       split = many_row_split(P, M);
+      P->many_us = split.us;
     } else {
       split.waves = M >= 256 ? 8 : 4;
     }

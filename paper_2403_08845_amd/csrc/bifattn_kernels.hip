@@ -1418,9 +1418,10 @@ __device__ __forceinline__ void ctx_wide_block(const PartialsParams& P, unsigned
 // NW / 4 of the n_dec_blocks decode work-groups, whose waves are independent:
 // the context part is bound by its chain of products and softmax, the decode
 // part by HBM, and the dispatcher fills the slots the context part leaves.
-// Against a launch behind it or on a second stream (us per step): MQA, 128
-// samples over 16k, 65.2 -> 56.7; 4 draft tokens, 32 samples over 8k, 94.5 ->
-// 81.4; ragged GQA, 256 samples over 32k, 221.6 -> 216.9.
+// Against a launch behind it or on a second stream (us per step, timed in turn):
+// MQA, 128 samples over 16k, 64.5 -> 56.2; 4 draft tokens, 32 samples over 8k,
+// 94.3 -> 81.2. Ragged GQA, 256 samples over 32k, is as fast either way (217):
+// its 160 context work-groups fill their CUs and the decode ones run on the rest.
 template <int D, int NW, int NB, int SK, typename KV, int NTD, bool R>
 __device__ __forceinline__ void ctx_wide_body(const PartialsParams& P) {
   constexpr int QB = NTD * (D / 32) * 64 * 16;  // bytes of a decode wave's Q^T operands
