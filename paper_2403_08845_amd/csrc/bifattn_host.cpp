@@ -287,7 +287,11 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
     // save). Measured, long chunks against these (us per step, bf16, d = 128):
     // b 5, h 32, g 8, m_c 3001 19.7 -> 13.8; m_c 12000 29.6 -> 19.8; b 20,
     // h 8, g 4, m_c 25000 44.6 -> 30.3; b 16, h = g = 32, m_c 8192, m_d 256
-    // 38.0 -> 37.1 (1536 keys; 1024: 40.1). With four query tiles per wave one
+    // 38.0 -> 37.1 (1536 keys; 1024: 40.1). Somewhat more work-groups than CUs
+    // are the worst of both: a few CUs hold two (b 2, h 80, g 40, 4 tokens, m_c
+    // 10456: 280 of 1536 keys 48.9, 240 of 1792 40.0; b 3, h = g = 40, m_c 8792 41.2,
+    // 33.2), so they are cut to one each. Over 260 layers the chunks are 2.5%
+    // slower than the best of thirteen, long ones throughout 28%. With four query tiles per wave one
     // work-group fills a CU, and a quarter more than an even share each leaves
     // some free for the decode ones (h 1536, g 32, m_c 3079, m_d 1024: 512 keys
     // 41.0, 1024 34.4, 640 35.9).
@@ -298,7 +302,13 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
       const int64_t all = (int64_t)d.g * d.m_c + units * d.m_d_max;  // keys of every unit
       const int64_t share = M <= 32 ? ceil_div(2 * all, 2 * kCUs) : ceil_div(5 * all, 4 * kCUs);
       const int64_t even = std::max<int64_t>(256, share);
-      if (even < keys) keys = round_up(ceil_div(d.m_c, ceil_div(d.m_c, even)), step);
+      if (even < keys) {
+        int64_t S = ceil_div(d.m_c, even);
+        if (M <= 32 && d.g * S > kCUs && d.g * S <= kCUs * 7 / 6 &&
+            ceil_div(d.m_c, kCUs / d.g) <= long_keys)
+          S = kCUs / d.g;
+        keys = round_up(ceil_div(d.m_c, S), step);
+      }
     }
     P->ctx_keys = (int)round_up(env_int("BIFATTN_CTX_KEYS", (int)keys), step);
     P->ctx_row_blocks = 1;

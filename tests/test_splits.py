@@ -281,3 +281,15 @@ def test_noalloc_with_longer_chunks(case):
     rt = np.arange(ri.size, dtype=np.int32) % n
     out = outs[1].cpu().double().numpy().reshape(b, h, n, d)[ri, rj, rt]
     assert_parity(out, oracle.attention_rows(**x, rows_i=ri, rows_j=rj, rows_t=rt), str(case), x=x)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,n", [((2, 80, 40, 128, 10456, 116), 4), ((3, 40, 40, 128, 8792, 14), 1),
+                                     ((4, 32, 32, 128, 3174, 683), 1), ((2, 96, 24, 64, 16186, 486), 2)])
+def test_few_row_context_work_groups_fill_whole_cus(shape, n):
+    """Not a few more context work-groups than CUs (160 to 280 of them with the
+    even share alone)."""
+    with bif.Plan(*shape, n=n) as plan:
+        info = plan.info()
+        assert info["ctx_kernel"] == 0
+        assert info["ctx_blocks"] <= 256 or info["ctx_blocks"] > 298, info
