@@ -304,9 +304,10 @@ bifattn_status_t plan_splits(bifattn_plan_s* P, bool allow_fork = true, bool coa
       const int64_t even = std::max<int64_t>(256, share);
       if (even < keys) {
         int64_t S = ceil_div(d.m_c, even);
-        if (M <= 32 && d.g * S > kCUs && d.g * S <= kCUs * 7 / 6 &&
-            ceil_div(d.m_c, kCUs / d.g) <= long_keys)
-          S = kCUs / d.g;
+        const int64_t whole = kCUs / d.g;  // splits of one work-group per CU, 0 if g alone is more
+        if (M <= 32 && d.g * S > kCUs && d.g * S <= kCUs * 7 / 6 && whole > 0 &&
+            ceil_div(d.m_c, whole) <= long_keys)
+          S = whole;
         keys = round_up(ceil_div(d.m_c, S), step);
       }
     }

@@ -81,6 +81,15 @@ def test_noalloc_takes_a_problem_that_fits(case):
     assert _noalloc_status(*case) != bif.ESCRATCH
 
 
+@pytest.mark.parametrize("g", [1, 2, 85, 128, 255, 256, 257, 270, 298, 299, 600])
+@pytest.mark.parametrize("p", [1, 8, 33])
+def test_splits_of_any_number_of_groups(g, p):
+    """Groups around the number of CUs, context lengths around the chunk bounds."""
+    for m_c in (1, 200, 256, 257, 300, 511, 513, 1000, 2049, 9000):
+        for b in (1, 3, 40):
+            assert _noalloc_status(b, g * p, g, 128, m_c, 16) != bif.OK  # no crash: EALIGN, EHIP ...
+
+
 def test_noalloc_refuses_what_cannot_fit():
     # the outputs' own partials: 64 rows of 4000 groups, one split, four decode waves
     assert _noalloc_status(64, 4000, 4000, 128, 100, 100) == bif.ESCRATCH
